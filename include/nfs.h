@@ -83,7 +83,10 @@ enum { NFS_IN_U16 = 0, NFS_IN_F32 = 1 };
  *                  e_t the largest integer for which
  *                  2^e_t * sigma_t * sum_x |u_t(x) - u_ref(x)| <= 65504 (no
  *                  overflow), 4 bytes per mode.
- * Differences, squares and sums are FP32 in every case (precision form). */
+ * Differences, squares and sums are FP32 in every case (precision form), or,
+ * for windows with many delays, exact sums of whole numbers: a mode's values
+ * in the window scaled by one power of two to at most 2^25 in magnitude and
+ * rounded (their differences then carry no further rounding). */
 enum { NFS_SPEC_F32 = 0, NFS_SPEC_BF16 = 1, NFS_SPEC_F16 = 2 };
 /* Per-mode pair accumulation.
  *   NFS_ACC_PLAIN: FP32 running sums;
@@ -170,8 +173,10 @@ nfs_status nfs_push_frames(nfs_handle h, const void* frames, int64_t count);
  * NFS_E_STATE. count == 0 is a no-op. */
 nfs_status nfs_push_host_frames(nfs_handle h, const void* frames, int64_t count);
 
-/* Empirical tuning of the pair kernel's launch shape (modes per workgroup
- * and waves summing lags) for each group of lags: times every shape the
+/* Empirical tuning of the launch shape (modes per workgroup and waves summing
+ * lags) of the pair kernel that forms every difference, for each group of
+ * lags (windows with many delays are summed on the matrix cores instead and
+ * have no shape to choose): times every shape the
  * kernel supports on the frames pushed so far (all of them while the ring
  * holds them all, else the frames whose partners are all still resident;
  * sums go to scratch memory, the plan's sums are not touched) and keeps the

@@ -51,6 +51,9 @@ struct nfs_plan_s {
   int32_t* tiles = nullptr;     // tiled slot layout (see ring_slot)
   int32_t* lags = nullptr;
   std::vector<nfs::LagGroup> groups;  // pair launch shapes (layout's, or tuned)
+  // Delay groups of the matrix-core pair kernel: for windows that fit one
+  // launch, and for windows that are cut.
+  std::vector<nfs::MxGroup> mx_whole, mx_cut;
   int64_t t_pushed = 0;  // frames pushed
   int64_t t_done = 0;    // frames whose pairs (as the later frame) are summed
   // No pair launch since the sums were reset: the next one stores its sums
@@ -115,10 +118,65 @@ nfs_status hip_fail(nfs_plan_s* h, hipError_t e, const char* where) {
   return fail(h, NFS_E_HIP, std::string(where) + ": " + hipGetErrorString(e));
 }
 
+// Largest delay of a group that has a pair with targets below T1 (-1: none).
+int64_t last_lag(const nfs_plan_s* h, const nfs::MxGroup& g, int64_t T1) {
+  for (int l = g.first + g.count - 1; l >= g.first; --l)
+    if (h->L.lags[size_t(l)] < T1) return h->L.lags[size_t(l)];
+  return -1;
+}
+
+// The delay groups the matrix-core kernel would sum targets [T0, T1) in:
+// those for windows that fit one launch if this one does.
+const std::vector<nfs::MxGroup>& mx_groups_for(const nfs_plan_s* h, int64_t T0, int64_t T1) {
+  for (const nfs::MxGroup& g : h->mx_whole) {
+    const int64_t ta = h->L.lags[size_t(g.first)], tb = last_lag(h, g, T1);
+    if (tb >= 0 && nfs::mx_shape(std::max(T0, ta), T1, ta, tb).pl > nfs::kMxPlane)
+      return h->mx_cut;
+  }
+  return h->mx_whole;
+}
+
+// Sum pairs whose later frame is in [T0, T1) on the matrix cores.
+hipError_t flush_pairs_mx(nfs_plan_s* h, const std::vector<nfs::MxGroup>& groups, int64_t T0,
+                          int64_t T1) {
+  const nfs::Layout& L = h->L;
+  nfs::MxTables tab;
+  for (const nfs::MxGroup& g : groups) {
+    const int64_t ta = L.lags[size_t(g.first)], tb = last_lag(h, g, T1);
+    bool assign = h->sums_fresh;
+    if (tb < 0 && !assign) continue;
+    // Targets before the smallest delay have no partner; a group without a
+    // pair only has its sums set to 0.
+    int64_t t = tb < 0 ? T1 - 1 : std::max(T0, ta);
+    while (t < T1) {
+      const int64_t e = tb < 0 ? T1 : nfs::mx_cut(t, T1, ta, tb);
+      nfs::MxShape s = nfs::mx_shape(t, e, ta, tb < 0 ? ta : tb);
+      nfs::mx_workgroup(&s, L.slots);
+      nfs::mx_tables(L.lags, g, t, e, &tab);
+      hipError_t err = nfs::launch_pairs_mx(
+          h->ring, L.spec_dtype, h->refspec, h->fscale, L.slots, L.mode_stride, L.capacity, s,
+          tab, h->lags + g.first, g.count, h->acc + g.first,
+          h->comp ? h->comp + g.first : nullptr, L.n_lags, assign, h->work + 1, h->stream);
+      if (err != hipSuccess) return err;
+      assign = false;
+      t = e;
+    }
+  }
+  return hipSuccess;
+}
+
 // Sum pairs whose later frame is in [t_done, t_pushed).
 nfs_status flush_pairs(nfs_plan_s* h) {
   if (h->t_done >= h->t_pushed) return NFS_OK;
   const nfs::Layout& L = h->L;
+  const std::vector<nfs::MxGroup>& mx = mx_groups_for(h, h->t_done, h->t_pushed);
+  if (nfs::mx_wins(L.lags, L.groups, mx, h->t_done, h->t_pushed)) {
+    hipError_t e = flush_pairs_mx(h, mx, h->t_done, h->t_pushed);
+    if (e != hipSuccess) return hip_fail(h, e, "pair kernel launch");
+    h->sums_fresh = false;
+    h->t_done = h->t_pushed;
+    return NFS_OK;
+  }
   for (const nfs::LagGroup& g : h->groups) {
     hipError_t e = nfs::launch_pairs(h->ring, L.spec_dtype, L.accum == NFS_ACC_KAHAN,
                                      h->refspec, h->fscale, L.slots, L.mode_stride,
@@ -299,6 +357,8 @@ nfs_status nfs_plan(const nfs_desc* desc, void* workspace, size_t bytes, void* s
   }
   const nfs::Layout& L = h->L;
   h->groups = L.groups;
+  h->mx_whole = nfs::mx_groups(L.lags, 0);
+  h->mx_cut = nfs::mx_groups(L.lags, nfs::kMxSpan);
   h->stream = static_cast<hipStream_t>(stream);
   h->ws = static_cast<char*>(workspace);
   h->window = desc->window;

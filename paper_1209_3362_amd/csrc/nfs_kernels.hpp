@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "pair_matrix.hpp"
+
 namespace nfs {
 
 // Row pass (per image row: real-to-complex transform of n pixels to the
@@ -91,6 +93,18 @@ hipError_t launch_pairs(const void* ring, int spec, bool kahan, const float2* re
                         int n_lags, int max_lag, float* acc, int acc_pitch, bool assign,
                         int modes, int hist, int waves, int per_wave, size_t lds,
                         unsigned long long* work, float* comp, hipStream_t s);
+
+// The same sums for the window and tables of one launch of the matrix-core
+// kernel (mx_shape, mx_tables): targets [s.t0, s.t1) and the group's delays
+// lags[0 .. n_lags), whose sums start at acc[m * acc_pitch]. Delays of s.t1
+// or more have no pair and are set to 0 with `assign`. comp (or null): Kahan
+// compensation of acc across launches.
+hipError_t launch_pairs_mx(const void* ring, int spec, const float2* refspec,
+                           const float4* fscale, int64_t n_modes, int64_t mode_stride,
+                           int64_t capacity, const MxShape& s, const MxTables& tab,
+                           const int32_t* lags, int n_lags, float* acc, float* comp,
+                           int acc_pitch, bool assign, unsigned long long* work,
+                           hipStream_t stream);
 
 // Azimuthal binning from the sums acc [slots][n_lags] (mode-major): segment
 // partials over the binning table bin_slots (entries 2 * slot + (k_x > 0),
