@@ -217,12 +217,87 @@ nfs_status clear_sums(nfs_plan_s* h) {
   return NFS_OK;
 }
 
+// Where a transform batch keeps its row-pass intermediate, row sums and
+// k_x = n/2 values.
+struct BatchScratch {
+  float2* inter;
+  double* rowsum;
+  double* rowabs;
+  float* nyq;
+};
+
+BatchScratch plan_scratch(const nfs_plan_s* h) {
+  return {h->inter, h->rowsum, h->rowabs, h->nyq};
+}
+
+// Scratch of b frames laid out from `base` on, and its size.
+size_t scratch_layout(const nfs_plan_s* h, int64_t b, char* base, BatchScratch* out) {
+  const nfs::Layout& L = h->L;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* at = base + off;
+    off = nfs::align_up(off + bytes, nfs::kAlign);
+    return at;
+  };
+  out->inter = reinterpret_cast<float2*>(take(size_t(b) * L.n * L.h * 8));
+  out->rowsum = reinterpret_cast<double*>(take(size_t(b) * L.n * 8));
+  out->rowabs = h->rowabs ? reinterpret_cast<double*>(take(size_t(b) * L.n * 8)) : nullptr;
+  out->nyq = h->nyq ? reinterpret_cast<float*>(take(size_t(b) * L.n * 4)) : nullptr;
+  return off;
+}
+
 // Frames of the next transform batch out of `left` still to push: at most
 // one batch, and no more than the ring can take beyond the largest lag.
 int64_t next_batch(const nfs_plan_s* h, int64_t left) {
   const int64_t room = h->L.capacity - h->L.max_lag;  // >= 1 by construction
   int64_t b = left < h->L.batch ? left : h->L.batch;
   return b < room ? b : room;
+}
+
+// The same for frames in device memory, with the batch's scratch. A plan whose
+// largest lag nearly fills its ring reserves an intermediate of few frames
+// (one for all N - 1 delays of a resident stack), but until the ring wraps
+// nothing is evicted and memory lies idle: the sums before their first pair
+// launch, and the ring slots behind the batch. The largest batch that either
+// holds is taken: one-frame launches take their launch latency each and fill a
+// few of the 256 CUs (2048 frames of 512 x 512 with all 2047 delays: 16 batches
+// instead of 2048, 42.0 -> 11.4 ms a pass; 32 frames of 32 x 32: 279 -> 66 us).
+int64_t next_batch(const nfs_plan_s* h, int64_t left, BatchScratch* scratch) {
+  const nfs::Layout& L = h->L;
+  *scratch = plan_scratch(h);
+  int64_t best = next_batch(h, left);
+  const int64_t free_slots = L.capacity - h->t_pushed;
+  const size_t frame = size_t(L.n) * L.h * 8;
+  const int64_t want = std::min({left, free_slots, int64_t(nfs::kMaxBatch),
+                                 std::max<int64_t>(1, int64_t(nfs::kBatchBytes / frame))});
+  auto fits = [&](int64_t b, char* base, size_t room) {
+    BatchScratch t;
+    return scratch_layout(h, b, base, &t) <= room;
+  };
+  auto consider = [&](auto&& base_of, auto&& room_of) {
+    int64_t lo = best, hi = want;  // the largest b in (best, want] that fits, by bisection
+    while (lo < hi) {
+      const int64_t mid = lo + (hi - lo + 1) / 2;
+      if (fits(mid, base_of(mid), room_of(mid))) lo = mid; else hi = mid - 1;
+    }
+    if (lo > best) {
+      best = lo;
+      scratch_layout(h, lo, base_of(lo), scratch);
+    }
+  };
+  if (h->fused) return best;
+  if (want > best && h->sums_fresh) {
+    const size_t sums = size_t(L.n_lags) * L.mode_stride * 4;
+    consider([&](int64_t) { return reinterpret_cast<char*>(h->acc); },
+             [&](int64_t) { return sums; });
+  }
+  if (want > best) {
+    const size_t slot = size_t(L.mode_stride) * L.mode_bytes;  // a multiple of kAlign
+    char* ring = static_cast<char*>(h->ring);
+    consider([&](int64_t b) { return ring + size_t(h->t_pushed + b) * slot; },
+             [&](int64_t b) { return size_t(L.capacity - h->t_pushed - b) * slot; });
+  }
+  return best;
 }
 
 // Sum the pending pairs if pushing `b` more frames would overwrite a
@@ -239,7 +314,8 @@ nfs_status make_room(nfs_plan_s* h, int64_t b) {
 // Normalise, transform and store `b` frames (device memory, b <= the batch
 // size, after the reference frame is set) as frames [t, t + b), each in
 // ring slot (its frame index) mod capacity.
-nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_t t) {
+nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_t t,
+                               const BatchScratch& w) {
   const nfs::Layout& L = h->L;
   if (h->fused) {
     // Bounded waits: about 2^22 polls (seconds) before a stuck wait gives up
@@ -260,14 +336,14 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
     return NFS_OK;
   }
   hipError_t e = nfs::launch_row_pass(L.n, L.in_dtype, src, h->ref, h->window, int(b),
-                                      h->inter, h->rowsum, h->rowabs, h->nyq, h->tw, h->stream);
+                                      w.inter, w.rowsum, w.rowabs, w.nyq, h->tw, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "row pass launch");
-  e = nfs::launch_col_pass(L.n, false, L.spec_dtype, h->inter, h->rowsum, h->rowabs, int(b), t,
+  e = nfs::launch_col_pass(L.n, false, L.spec_dtype, w.inter, w.rowsum, w.rowabs, int(b), t,
                            L.capacity, L.mode_stride, L.slots, h->tiles, h->tw, h->ring,
                            h->refspec, h->refscal, h->fscale, h->status, h->work, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "column pass launch");
   if (L.full) {
-    e = nfs::launch_nyquist_col(L.n, false, L.spec_dtype, h->nyq, int(b), t, L.capacity,
+    e = nfs::launch_nyquist_col(L.n, false, L.spec_dtype, w.nyq, int(b), t, L.capacity,
                                 L.mode_stride, L.nyq_slot, h->tw, h->fscale, h->ring,
                                 h->refspec, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "Nyquist column launch");
@@ -275,9 +351,9 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
   return NFS_OK;
 }
 
-// Normalise, transform and store `b` frames (device memory, b <= the batch
-// size) as frames [t_pushed, t_pushed + b); make_room must precede it.
-nfs_status transform_batch(nfs_plan_s* h, const char* src, int64_t b) {
+// Normalise, transform and store `b` frames (device memory, as many as the
+// scratch holds) as frames [t_pushed, t_pushed + b); make_room must precede it.
+nfs_status transform_batch(nfs_plan_s* h, const char* src, int64_t b, const BatchScratch& w) {
   const nfs::Layout& L = h->L;
   hipError_t e = hipSuccess;
   if (h->t_pushed == 0) {
@@ -300,7 +376,7 @@ nfs_status transform_batch(nfs_plan_s* h, const char* src, int64_t b) {
                                   h->refspec, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "reference transform launch");
   }
-  nfs_status st = transform_into_ring(h, src, b, h->t_pushed);
+  nfs_status st = transform_into_ring(h, src, b, h->t_pushed, w);
   if (st != NFS_OK) return st;
   h->t_pushed += b;
   return NFS_OK;
@@ -477,10 +553,12 @@ nfs_status nfs_push_frames(nfs_handle h, const void* frames, int64_t count) {
   if (!frames) return fail(h, NFS_E_ARG, "frames is NULL");
   int64_t i = 0;
   while (i < count) {
-    const int64_t b = next_batch(h, count - i);
+    BatchScratch w;
+    const int64_t b = next_batch(h, count - i, &w);
     nfs_status st = make_room(h, b);
     if (st == NFS_OK)
-      st = transform_batch(h, static_cast<const char*>(frames) + size_t(i) * h->L.frame_bytes, b);
+      st = transform_batch(h, static_cast<const char*>(frames) + size_t(i) * h->L.frame_bytes, b,
+                           w);
     if (st != NFS_OK) return st;
     i += b;
   }
@@ -514,7 +592,7 @@ nfs_status nfs_push_host_frames(nfs_handle h, const void* frames, int64_t count)
     if (st != NFS_OK) return st;
     e = hipStreamWaitEvent(h->stream, h->copied[j], 0);
     if (e != hipSuccess) return hip_fail(h, e, "host frame upload");
-    st = transform_batch(h, h->stage[j], b);
+    st = transform_batch(h, h->stage[j], b, plan_scratch(h));
     if (st != NFS_OK) return st;
     e = hipEventRecord(h->freed[j], h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "staging event");
@@ -682,7 +760,8 @@ nfs_status nfs_backward(nfs_handle h, const double* dL_dD, const void* frames,
       while (have < need) {
         const int64_t c = need - have < L.batch ? need - have : L.batch;
         nfs_status st = transform_into_ring(
-            h, static_cast<const char*>(frames) + size_t(have) * L.frame_bytes, c, have);
+            h, static_cast<const char*>(frames) + size_t(have) * L.frame_bytes, c, have,
+            plan_scratch(h));
         if (st != NFS_OK) return st;
         have += c;
       }
