@@ -174,10 +174,10 @@ nfs_status nfs_push_frames(nfs_handle h, const void* frames, int64_t count);
 nfs_status nfs_push_host_frames(nfs_handle h, const void* frames, int64_t count);
 
 /* Empirical tuning of the launch shape (modes per workgroup and waves summing
- * lags) of the pair kernel that forms every difference, for each group of
- * lags (windows with many delays are summed on the matrix cores instead and
- * have no shape to choose): times every shape the
- * kernel supports on the frames pushed so far (all of them while the ring
+ * lags) of the pair kernel that walks a window's frames with their history,
+ * for each group of lags (windows with many delays are summed on the matrix
+ * cores instead, short ones by a kernel that holds all of their frames; those
+ * have no shape to choose): times every shape the kernel supports on the frames pushed so far (all of them while the ring
  * holds them all, else the frames whose partners are all still resident;
  * sums go to scratch memory, the plan's sums are not touched) and keeps the
  * fastest for the plan's later pair sums. The choice

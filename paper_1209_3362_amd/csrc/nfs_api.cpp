@@ -178,13 +178,21 @@ nfs_status flush_pairs(nfs_plan_s* h) {
     return NFS_OK;
   }
   for (const nfs::LagGroup& g : h->groups) {
-    hipError_t e = nfs::launch_pairs(h->ring, L.spec_dtype, L.accum == NFS_ACC_KAHAN,
-                                     h->refspec, h->fscale, L.slots, L.mode_stride,
-                                     L.capacity, h->t_done,
-                                     h->t_pushed, h->lags + g.first, g.count, g.max_lag,
-                                     h->acc + g.first, L.n_lags, h->sums_fresh, g.modes,
-                                     g.hist, g.waves, g.per_wave, g.lds, h->work + 1,
-                                     h->comp ? h->comp + g.first : nullptr, h->stream);
+    hipError_t e = hipSuccess;
+    nfs::WindowShape w;
+    if (L.accum == NFS_ACC_PLAIN && nfs::window_shape(g, L.slots, h->t_done, h->t_pushed, &w)) {
+      e = nfs::launch_pairs_window(h->ring, L.spec_dtype, h->refspec, h->fscale, L.slots,
+                                   L.mode_stride, L.capacity, h->t_done, h->t_pushed,
+                                   h->lags + g.first, w, h->acc + g.first, L.n_lags,
+                                   h->sums_fresh, h->work + 1, h->stream);
+    } else {
+      e = nfs::launch_pairs(h->ring, L.spec_dtype, L.accum == NFS_ACC_KAHAN, h->refspec,
+                            h->fscale, L.slots, L.mode_stride, L.capacity, h->t_done,
+                            h->t_pushed, h->lags + g.first, g.count, g.max_lag,
+                            h->acc + g.first, L.n_lags, h->sums_fresh, g.modes, g.hist,
+                            g.waves, g.per_wave, g.lds, h->work + 1,
+                            h->comp ? h->comp + g.first : nullptr, h->stream);
+    }
     if (e != hipSuccess) return hip_fail(h, e, "pair kernel launch");
   }
   h->sums_fresh = false;

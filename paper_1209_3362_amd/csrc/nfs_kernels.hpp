@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "pair_matrix.hpp"
+#include "pair_plan.hpp"
 
 namespace nfs {
 
@@ -93,6 +94,14 @@ hipError_t launch_pairs(const void* ring, int spec, bool kahan, const float2* re
                         int n_lags, int max_lag, float* acc, int acc_pitch, bool assign,
                         int modes, int hist, int waves, int per_wave, size_t lds,
                         unsigned long long* work, float* comp, hipStream_t s);
+
+// The sums of launch_pairs (plain accumulation) for a window whose frames
+// [T0 - w.pre, T1) fit the LDS; work: += the pairs summed.
+hipError_t launch_pairs_window(const void* ring, int spec, const float2* refspec,
+                               const float4* fscale, int64_t n_modes, int64_t mode_stride,
+                               int64_t capacity, int64_t T0, int64_t T1, const int32_t* lags,
+                               const WindowShape& w, float* acc, int acc_pitch, bool assign,
+                               unsigned long long* work, hipStream_t s);
 
 // The same sums for the window and tables of one launch of the matrix-core
 // kernel (mx_shape, mx_tables): targets [s.t0, s.t1) and the group's delays

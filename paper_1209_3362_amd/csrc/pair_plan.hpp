@@ -56,4 +56,23 @@ bool plan_group(const std::vector<int32_t>& lags, int first, int count, LagGroup
 // (at most kMaxLagsPerWave lags per wave; 12-wave workgroups for 6 or more).
 std::vector<LagGroup> group_candidates(const std::vector<int32_t>& lags, int first, int count);
 
+// Launch of the short-window kernel for one lag group: targets [T0, T1) and the
+// `pre` frames before them in LDS.
+constexpr int kWinLags = 4;   // most lags of a set
+constexpr int kWinGuard = 7;  // rows before the first frame that masked lanes read
+struct WindowShape {
+  int n_lags = 0;
+  int pre = 0;
+  int modes = 0;   // per workgroup: 16 or 32
+  int waves = 0;   // 4, or 8 with 16 modes
+  int sets = 0;    // near-equal runs of the group's lags
+  int slices = 0;  // of the blocks of targets, interleaved
+  size_t lds = 0;
+};
+
+// The shape for one lag group of a plan with n_modes slots; false where the
+// window is left to the group's other kernels.
+bool window_shape(const LagGroup& group, int64_t n_modes, int64_t T0, int64_t T1,
+                  WindowShape* w);
+
 }  // namespace nfs
