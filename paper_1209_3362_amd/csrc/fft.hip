@@ -474,6 +474,180 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
 }
 
 // ---------------------------------------------------------------------------
+// The column pass from n = 2048 on: the same inputs, outputs and scales as
+// col_pass_kernel, the DFT in three levels. With x[a + C b + M j] (j, b < 16, a <
+// C, M = 16 C): DFT over j in registers, twiddles W_n^{(a + C b) k2} (they depend
+// on the thread alone and stay in registers across frames), exchange, DFT over
+// b, twiddles W_M^{a kb} from LDS, exchange, DFT over a gives
+// X[k2 + 16 kb + 256 ka].
+// Bound by HBM (at n = 2048 a frame's 16.8 MB of intermediate and 13.2 MB of
+// FP32 modes). In two levels a thread held 64 points, a CU four waves and the
+// n / 32 twiddle gathers of each went through L1: 96 frames of 2048 x 2048 took
+// 1003 us, now 590 (4.9 TB/s); a 4096 x 4096 frame and its row pass 160, now 145.
+template <int N, bool REF, int SPEC>
+__global__ __launch_bounds__(Col3Cfg<N>::THREADS, 4) void col3_pass_kernel(
+    const float2* __restrict__ inter, const double* __restrict__ rowsum,
+    const double* __restrict__ rowabs, const double* __restrict__ refscal,
+    float4* __restrict__ fscale, int32_t* __restrict__ status, int nframes, int per_group,
+    int64_t t0, int64_t capacity, int64_t mode_stride, int64_t n_modes,
+    const int32_t* __restrict__ tiles, const float2* __restrict__ tw, char* __restrict__ ring,
+    float2* __restrict__ refspec, unsigned long long* __restrict__ work) {
+  static_assert(!REF || SPEC == kSpecF32, "the reference transform is kept in FP32");
+  constexpr bool F16 = SPEC == kSpecF16;
+  constexpr uint32_t MODE_BYTES = SPEC == kSpecF32 ? 8u : 4u;
+  using C3 = Col3Cfg<N>;
+  constexpr int M = C3::M, C = C3::C, CW = C3::CW, CP = C3::CP, S2 = C3::S2;
+  constexpr int THREADS = C3::THREADS, GROUPS = C3::GROUPS, NWAVES = THREADS / 64;
+  constexpr int Q = 16 / C;  // last-level transforms per thread
+  static_assert(CW == ColCfg<N>::TWD, "a workgroup reads one tile of the intermediate");
+  __shared__ float2 lds[CW * CP];
+  __shared__ float2 twm[M];
+  __shared__ double red[NWAVES];
+  __shared__ double red_abs[F16 ? NWAVES : 1];
+
+  // Neighbouring column groups of a frame share an XCD (see col_pass_kernel).
+  int bid = blockIdx.x;
+  if (gridDim.x % 8 == 0) bid = (bid % 8) * int(gridDim.x / 8) + bid / 8;
+  const int grp = bid % GROUPS;
+  const int f_begin = (bid / GROUPS) * per_group;
+  const int f_end = min(nframes, f_begin + per_group);
+  const int tid = threadIdx.x;
+  const int c = tid % CW, t = tid / CW;
+  const int kx = grp * CW + c;
+  for (int i = tid; i < M; i += THREADS) twm[i] = tw[16 * i];
+  float2 w1[16];  // W_n^{t k2}
+#pragma unroll
+  for (int k2 = 1; k2 < 16; ++k2) w1[k2] = tw[(t * k2) & (N - 1)];
+  // Outputs of this thread: rows t + M q + 256 ka of column kx. ring_slot with
+  // the tile, which the workgroup's columns share, looked up once: rows up to R
+  // and from n - R on are kept, those of a full plan (R = n/2) all in place.
+  const int tile8 = grp * CW / 8;
+  const int R = tiles[N / 16 + 1 + tile8];
+  const int skip = R >= N / 2 ? 0 : N - 2 * R - 1;
+  const int slot0 = tiles[tile8] + (kx & 7);
+  auto store_offset = [&](int r) -> uint32_t {
+    return r <= R || r >= N - R ? uint32_t(slot0 + (r <= R ? r : r - skip) * 8) * 8u : kDropOffset;
+  };
+  const uint32_t spec_bytes = uint32_t(n_modes) * MODE_BYTES;
+  double s_ref = 0.0, sigma_ref = 0.0;
+  if constexpr (!REF) {
+    s_ref = refscal[0];
+    sigma_ref = refscal[1];
+  }
+  float2* col = lds + c * CP;
+  auto load_cols = [&](float2 (&v)[16], int f) {
+    const BufferRsrc src =
+        make_buffer(const_cast<float2*>(inter) + (int64_t(f) * GROUPS + grp) * N * CW, N * CW * 8);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = buffer_load_f2(src, tid * 8, M * j * CW * 8);
+  };
+  float2 v[16];
+  if (f_begin < f_end) load_cols(v, f_begin);
+  int64_t slot = (t0 + f_begin) % capacity;
+  __syncthreads();
+
+  for (int f = f_begin; f < f_end; ++f) {
+    double part = 0.0, part_abs = 0.0;
+    if constexpr (!REF) {
+      for (int y = tid; y < N; y += THREADS) part += rowsum[int64_t(f) * N + y];
+    }
+    if constexpr (F16) {
+      for (int y = tid; y < N; y += THREADS) part_abs += rowabs[int64_t(f) * N + y];
+    }
+    dft<16>(v);
+    static_for<16>([&](auto K2) {
+      constexpr int k2 = decltype(K2)::value;
+      float2 y = v[bitrev<16>(k2)];
+      if constexpr (k2 != 0) y = cmul(y, w1[k2]);
+      col[k2 * M + t] = y;
+    });
+    if constexpr (!REF) {
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o, 64);
+      if ((tid & 63) == 0) red[tid >> 6] = part;
+    }
+    if constexpr (F16) {
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) part_abs += __shfl_xor(part_abs, o, 64);
+      if ((tid & 63) == 0) red_abs[tid >> 6] = part_abs;
+    }
+    __syncthreads();
+    // What follows from the thread index is computed per frame: kept across the
+    // frames it would spill.
+    int ts = t;
+    asm volatile("" : "+v"(ts));
+    const int a = ts % C, k2 = ts / C;
+    float2 u[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) u[b] = col[k2 * M + a + C * b];
+    dft<16>(u);
+    __syncthreads();  // the first exchange is read
+    static_for<16>([&](auto KB) {
+      constexpr int kb = decltype(KB)::value;
+      float2 y = u[bitrev<16>(kb)];
+      if constexpr (kb != 0) y = cmul(y, twm[(a * kb) & (M - 1)]);
+      col[a * S2 + k2 + 16 * kb] = y;
+    });
+    __syncthreads();
+
+    float scale = 1.f;
+    if constexpr (!REF) {
+      double tot = red[0];
+#pragma unroll
+      for (int w = 1; w < NWAVES; ++w) tot += red[w];
+      const double S = s_ref + tot;
+      const bool bad = !(S > 0.0) || !isfinite(S);
+      const double sigma = bad ? 0.0 : double(N) * double(N) / S;
+      int e = 0;
+      if constexpr (F16) {
+        double l1 = red_abs[0];
+#pragma unroll
+        for (int w = 1; w < NWAVES; ++w) l1 += red_abs[w];
+        e = f16_exponent(sigma * l1);  // bounds every |sigma * X(k)|
+      }
+      scale = float(ldexp(sigma, e));
+      if (grp == 0 && tid == 0) {
+        fscale[slot] =
+            make_float4(float(sigma), float(sigma - sigma_ref), float(ldexp(1.0, -e)), 0.f);
+        if (bad) atomicOr(status, 1);
+        if (work) atomicAdd(work, 1ull);  // work counter: frames transformed
+      }
+    }
+    if (f + 1 < f_end) load_cols(v, f + 1);
+    const BufferRsrc dst =
+        make_buffer(REF ? static_cast<void*>(refspec)
+                        : static_cast<void*>(ring + slot * mode_stride * int64_t(MODE_BYTES)),
+                    spec_bytes);
+    static_for<Q>([&](auto QQ) {
+      constexpr int q = decltype(QQ)::value;
+      float2 w[C];
+#pragma unroll
+      for (int i = 0; i < C; ++i) w[i] = col[i * S2 + t + M * q];
+      dft<C>(w);
+      static_for<C>([&](auto KA) {
+        constexpr int ka = decltype(KA)::value;
+        const uint32_t o = store_offset(ts + M * q + 256 * ka);
+        float2 X = w[bitrev<C>(ka)];
+        if constexpr (!REF) {
+          X.x *= scale;
+          X.y *= scale;
+        }
+        // Only output (q, ka) = (0, 0) of thread 0 of group 0 is k = 0.
+        if constexpr (q == 0 && ka == 0) {
+          if (o == 0) X = make_float2(0.f, 0.f);
+        }
+        if constexpr (SPEC == kSpecF32)
+          buffer_store(X, dst, o);
+        else
+          buffer_store_u32(SPEC == kSpecBF16 ? pack_bf16(X) : pack_f16(X), dst, o >> 1);
+      });
+    });
+    if (++slot == capacity) slot = 0;
+    __syncthreads();  // LDS is rewritten by the next frame
+  }
+}
+
+// ---------------------------------------------------------------------------
 // The k_x = n/2 column of full half-plane plans, one workgroup per frame:
 // Y(k_y) = sum_y x[y] W_n^{k_y y} of the row pass's real values x[y] =
 // X_y(n/2), by an iterative radix-2 transform in LDS (bit-reversed load,
@@ -890,15 +1064,24 @@ hipError_t col_launch(bool reference, int spec, const float2* inter, const doubl
                       const float2* tw, void* ring, float2* refspec,
                       double* refscal, float4* fscale, int32_t* status,
                       unsigned long long* work, hipStream_t s) {
-  using C = ColCfg<N>;
-  const int per = frames_per_group(nframes, C::GROUPS);
+  using C = std::conditional_t<(N >= 2048), Col3Cfg<(N >= 2048 ? N : 2048)>, ColCfg<N>>;
+  constexpr int threads = C::THREADS;
+  // 128 threads and 40 KB of LDS (n = 512): four workgroups to a CU. A launch of
+  // 128 frames takes 45.6 us with 1024 workgroups, 55.4 with 512; n = 1024 (256
+  // threads, two to a CU) 44.7 with 512, 48.1 with 1024.
+  const int per = frames_per_group(nframes, C::GROUPS, threads < 256 ? 1024 : 512);
   const int64_t blocks = int64_t(C::GROUPS) * ((nframes + per - 1) / per);
   char* ringb = static_cast<char*>(ring);
-#define NFS_COL_GO(REFV, SPECV)                                                                \
-  hipLaunchKernelGGL((col_pass_kernel<N, REFV, SPECV>), dim3(unsigned(blocks)),               \
-                     dim3(C::THREADS), 0, s, inter, rowsum, rowabs, refscal, fscale, status,   \
-                     nframes, per, t0, capacity, mode_stride, n_modes, tiles, tw, ringb,     \
-                     refspec, work)
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(threads), 0, s, inter, rowsum,
+                       rowabs, refscal, fscale, status, nframes, per, t0, capacity, mode_stride,
+                       n_modes, tiles, tw, ringb, refspec, work);
+  };
+#define NFS_COL_GO(REFV, SPECV)                        \
+  if constexpr (N >= 2048)                             \
+    go(col3_pass_kernel<N, REFV, SPECV>);              \
+  else                                                 \
+    go(col_pass_kernel<N, REFV, SPECV>)
   if (reference) {
     hipLaunchKernelGGL(ref_scale_kernel, dim3(1), dim3(256), 0, s, N, rowsum, refscal, status);
     NFS_COL_GO(true, kSpecF32);

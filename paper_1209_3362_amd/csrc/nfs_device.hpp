@@ -83,6 +83,14 @@ __device__ __forceinline__ void buffer_store(float2 v, BufferRsrc r, uint32_t by
   __builtin_amdgcn_raw_buffer_store_b64(bits, r, static_cast<int>(byte_offset), 0, 0);
 }
 
+__device__ __forceinline__ float2 buffer_load_f2(BufferRsrc r, uint32_t byte_offset,
+                                                 uint32_t uniform_offset) {
+  using U2 = __attribute__((ext_vector_type(2))) unsigned;
+  const U2 bits = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(byte_offset),
+                                                       static_cast<int>(uniform_offset), 0);
+  return make_float2(__uint_as_float(bits.x), __uint_as_float(bits.y));
+}
+
 // ---------------------------------------------------------------------------
 // Compile-time cos/sin of 2*pi*j/n, evaluated in double: the angle is split
 // into its octant and a remainder in [0, pi/4], where Taylor series converge
