@@ -88,11 +88,20 @@ __device__ __forceinline__ typename RawPair<T>::type load_pair(const T* p) {
 // to `per_group` frames of the batch, loading the next frame's pixels while
 // it transforms the current one. ABS: also write rowabs[f][y], the row's sum
 // of |what is transformed| (bounds every coefficient of the frame).
+// first (0 or 1; n <= kFirstMax): the batch starts a sequence and its frame 0 is
+// the reference (ref == frames). Frame 0 as it is, nothing subtracted, is then
+// transformed as one more frame `nframes` and copied to ref_out, and the
+// sequence's counters at `clear` are set to 0. As launches of their own the
+// reference's passes, copy and scale and the clearing took 10 of 48 us for
+// 64 frames of 128 x 128. One instance of the kernel does both kinds of batch,
+// so that a frame's bits do not depend on how it was pushed.
 template <int N, typename T, bool WIN, bool ABS>
 __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>())) void row_pass_kernel(
     const T* __restrict__ frames, const T* __restrict__ ref, const float* __restrict__ window,
     int nframes, int per_group, float2* __restrict__ inter, double* __restrict__ rowsum,
-    double* __restrict__ rowabs, float* __restrict__ nyq, const float2* __restrict__ tw) {
+    double* __restrict__ rowabs, float* __restrict__ nyq, const float2* __restrict__ tw,
+    int first, T* __restrict__ ref_out, uint32_t* __restrict__ clear) {
+  constexpr bool FIRST = N <= kFirstMax;
   using C = RowCfg<N>;
   using Raw = typename RawPair<T>::type;
   constexpr bool U16 = std::is_same<T, uint16_t>::value;
@@ -105,15 +114,18 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>(
   const int rl = tid / P1, j1 = tid % P1;
   const int rblk = blockIdx.x % RB;
   const int f_begin = (blockIdx.x / RB) * per_group;
-  const int f_end = min(nframes, f_begin + per_group);
+  const int f_end = min(FIRST ? nframes + first : nframes, f_begin + per_group);
   const int y = rblk * R + rl;
   float2* row_lds = lds + rl * PITCH;
+  if (FIRST && clear && blockIdx.x == 0)
+    for (int i = tid; i < kClearWords; i += THREADS) clear[i] = 0u;
 
   for (int i = tid; i < N; i += THREADS) twl[tw_skew(i)] = tw[i];
 
   // Up to 32 pixel pairs per thread the reference row stays in registers and
   // the next frame is prefetched; larger rows reload both from cache.
   constexpr bool CACHE = P2 <= 32;
+  static_assert(CACHE || !FIRST, "FIRST selects among the cached reference pairs");
   constexpr int NC = CACHE ? P2 : 1;
   Raw refv[NC], raw[NC];
   auto ref_pair = [&](int j2) -> Raw {
@@ -123,6 +135,7 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>(
     return load_pair(ref + int64_t(y) * N + 2 * (j1 + P1 * j2));
   };
   auto raw_pair = [&](int f, int j2) -> Raw {
+    if (FIRST && f == nframes) f = 0;
     return load_pair(frames + (int64_t(f) * N + y) * N + 2 * (j1 + P1 * j2));
   };
   auto load_raw = [&](int f) {
@@ -137,6 +150,15 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>(
   __syncthreads();  // the twiddle table is shared by all rows
 
   for (int f = f_begin; f < f_end; ++f) {
+    if constexpr (FIRST) {
+      if (f == nframes) {  // the reference, the last frame of its workgroups
+#pragma unroll
+        for (int j2 = 0; j2 < P2; ++j2) {
+          *reinterpret_cast<Raw*>(ref_out + int64_t(y) * N + 2 * (j1 + P1 * j2)) = raw[j2];
+          if constexpr (U16) refv[j2] = 0u; else refv[j2] = make_float2(0.f, 0.f);
+        }
+      }
+    }
     float2 v[P2];
     int si = 0, sia = 0;
     double sd = 0.0, sda = 0.0;
@@ -264,34 +286,46 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>(
 }
 
 // ---------------------------------------------------------------------------
-// Scale of the reference image from its row sums, in a fixed order
-// (strided partial sums, butterfly per wave, waves in index order):
-// refscal = {S_ref, n^2/S_ref}, sigma 0 (and bit 0 of *status) when S_ref
-// is not positive and finite. Frames' scales are formed in the column pass.
-__global__ __launch_bounds__(256) void ref_scale_kernel(int n, const double* __restrict__ rowsum,
-                                                        double* __restrict__ refscal,
-                                                        int32_t* __restrict__ status) {
-  __shared__ double red[4];
-  const int tid = threadIdx.x;
-  double s = 0.0;
-  for (int y = tid; y < n; y += 256) s += rowsum[y];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = s;
+// Sum of the reference image from its row sums, the same in every workgroup and
+// column kernel: 256 strided partial sums, butterfly per 64 of them, the four in
+// index order. red: 4 doubles of LDS; ends with a barrier.
+template <int N, int THREADS>
+__device__ __forceinline__ double reference_sum(const double* __restrict__ rowsum, double* red,
+                                                int tid) {
+  constexpr int LANES = THREADS < 64 ? THREADS : 64;  // of a (possibly partial) wave
+  static_assert(LANES == 64 || N <= LANES, "fewer lanes hold all rows");
+  if (tid < 4) red[tid] = 0.0;
   __syncthreads();
-  if (tid == 0) {
-    const double total = ((red[0] + red[1]) + red[2]) + red[3];
-    const bool bad = !(total > 0.0) || !isfinite(total);
-    refscal[0] = total;
-    refscal[1] = bad ? 0.0 : double(n) * double(n) / total;
-    if (bad) atomicOr(status, 1);
+  for (int p = tid; p < 256; p += THREADS) {
+    double s = 0.0;
+    for (int y = p; y < N; y += 256) s += rowsum[y];
+#pragma unroll
+    for (int o = LANES / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, LANES);
+    if ((p & 63) == 0) red[p >> 6] = s;
   }
+  __syncthreads();
+  return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// The scale that goes with it, refscal = {S_ref, n^2 / S_ref}; 0 (and bit 0 of
+// *status) when S_ref is not positive and finite. Frames' scales are formed in
+// the column pass.
+__device__ __forceinline__ double reference_sigma(int n, double total) {
+  return !(total > 0.0) || !isfinite(total) ? 0.0 : double(n) * double(n) / total;
+}
+__device__ __forceinline__ void write_reference_scale(double total, double sigma,
+                                                      double* __restrict__ refscal,
+                                                      int32_t* __restrict__ status) {
+  refscal[0] = total;
+  refscal[1] = sigma;
+  if (sigma == 0.0) atomicOr(status, 1);
 }
 
 // ---------------------------------------------------------------------------
 // Column pass over CW columns: DFT_N over the rows of each frame of the
 // group. REF: store the reference transform F[reference] unscaled in
-// refspec. Otherwise the rows were (frame - reference) of frame t0 + f:
+// refspec and its scale in refscal; so is frame `nframes` with first (see the row
+// pass), where every workgroup sums S_ref itself. Otherwise the rows were (frame - reference) of frame t0 + f:
 // every workgroup of the frame forms S = S_ref + (sum of its row sums) in
 // the same fixed order (strided partial sums, butterfly per wave, waves in
 // index order) and sigma = n^2 / S, stores sigma * X (X = F[frame -
@@ -308,12 +342,14 @@ __global__ __launch_bounds__(256) void ref_scale_kernel(int n, const double* __r
 template <int N, bool REF, int SPEC>
 __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_kernel(
     const float2* __restrict__ inter, const double* __restrict__ rowsum,
-    const double* __restrict__ rowabs, const double* __restrict__ refscal,
+    const double* __restrict__ rowabs, double* __restrict__ refscal,
     float4* __restrict__ fscale, int32_t* __restrict__ status, int nframes, int per_group,
     int64_t t0, int64_t capacity, int64_t mode_stride, int64_t n_modes,
     const int32_t* __restrict__ tiles, const float2* __restrict__ tw, char* __restrict__ ring,
-    float2* __restrict__ refspec, unsigned long long* __restrict__ work) {
+    float2* __restrict__ refspec, unsigned long long* __restrict__ work, int first) {
   static_assert(!REF || SPEC == kSpecF32, "the reference transform is kept in FP32");
+  constexpr bool FIRST = N <= kFirstMax;
+  static_assert(!(REF && FIRST), "the reference goes with a batch");
   constexpr bool F16 = SPEC == kSpecF16;
   constexpr uint32_t MODE_BYTES = SPEC == kSpecF32 ? 8u : 4u;
   using C = ColCfg<N>;
@@ -325,6 +361,7 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
   __shared__ float2 twl[C::TWL];
   __shared__ double red[NWAVES];
   __shared__ double red_abs[F16 ? NWAVES : 1];
+  __shared__ double red_ref[REF || FIRST ? 4 : 1];
 
   // Workgroups are dispatched round-robin over the 8 XCDs; renumber them so
   // neighbouring column groups of a frame (which write the two halves of
@@ -333,7 +370,7 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
   if (gridDim.x % 8 == 0) bid = (bid % 8) * int(gridDim.x / 8) + bid / 8;
   const int grp = bid % GROUPS;
   const int f_begin = (bid / GROUPS) * per_group;
-  const int f_end = min(nframes, f_begin + per_group);
+  const int f_end = min(FIRST ? nframes + first : nframes, f_begin + per_group);
   const int kx0 = grp * CW;
   const int tid = threadIdx.x;
   const int c = tid % CW, j1 = tid / CW;
@@ -372,11 +409,19 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
   if (CACHE && f_begin < f_end) load_cols(v, f_begin);
   float2* col_lds = lds + c * CP;
   int64_t slot = (t0 + f_begin) % capacity;
-  const uint32_t spec_bytes = uint32_t(n_modes) * MODE_BYTES;
   double s_ref = 0.0, sigma_ref = 0.0;
-  if constexpr (!REF) {
+  if (FIRST && first) {
+    s_ref = reference_sum<N, THREADS>(rowsum + int64_t(nframes) * N, red_ref, tid);
+    sigma_ref = reference_sigma(N, s_ref);
+  } else if constexpr (!REF) {
     s_ref = refscal[0];
     sigma_ref = refscal[1];
+  }
+  if constexpr (REF) {
+    if (grp == 0 && f_begin == 0) {
+      const double total = reference_sum<N, THREADS>(rowsum, red_ref, tid);
+      if (tid == 0) write_reference_scale(total, reference_sigma(N, total), refscal, status);
+    }
   }
   __syncthreads();
 
@@ -413,7 +458,10 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
     }
 
     float scale = 1.f;
-    if constexpr (!REF) {
+    const bool reference = FIRST && f == nframes;
+    if (FIRST && reference) {
+      if (grp == 0 && tid == 0) write_reference_scale(s_ref, sigma_ref, refscal, status);
+    } else if constexpr (!REF) {
       double tot = red[0];
 #pragma unroll
       for (int w = 1; w < NWAVES; ++w) tot += red[w];
@@ -435,39 +483,49 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
         if (work) atomicAdd(work, 1ull);  // work counter: frames transformed
       }
     }
-    const BufferRsrc dst =
-        make_buffer(REF ? static_cast<void*>(refspec)
-                        : static_cast<void*>(ring + slot * mode_stride * int64_t(MODE_BYTES)),
-                    spec_bytes);
-    static_for<Q>([&](auto QQ) {
-      constexpr int q = decltype(QQ)::value;
-      const int k2 = j1 + q * P1;
-      float2 w[P1];
+    // AS_REF: FP32 into refspec as it is; else scaled into the slot.
+    auto second = [&](auto AS_REF) {
+      constexpr bool F32 = SPEC == kSpecF32 || decltype(AS_REF)::value;
+      const bool into_ref = REF || (FIRST && reference);
+      const BufferRsrc dst =
+          make_buffer(into_ref ? static_cast<void*>(refspec)
+                               : static_cast<void*>(ring + slot * mode_stride * int64_t(MODE_BYTES)),
+                      uint32_t(n_modes) * (F32 ? 8u : 4u));
+      static_for<Q>([&](auto QQ) {
+        constexpr int q = decltype(QQ)::value;
+        const int k2 = j1 + q * P1;
+        float2 w[P1];
 #pragma unroll
-      for (int j = 0; j < P1; ++j) w[j] = col_lds[k2 * (P1 + 1) + j];
-      dft<P1>(w);
-      static_for<P1>([&](auto K1) {
-        constexpr int k1 = decltype(K1)::value;
-        uint32_t o;
-        if constexpr (CACHE) o = at[q][k1]; else o = store_offset(q, k1);
-        float2 X = w[bitrev<P1>(k1)];
-        if constexpr (!REF) {
-          X.x *= scale;
-          X.y *= scale;
-        }
-        // Only output (q, k1) = (0, 0) of thread 0 of group 0 is k = 0.
-        if constexpr (q == 0 && k1 == 0) {
-          if (o == 0) X = make_float2(0.f, 0.f);
-        }
-        if constexpr (SPEC == kSpecF32) {
-          buffer_store(X, dst, o);
-        } else {
-          // Offsets were computed for 8-byte modes; halving keeps the drop
-          // value out of range.
-          buffer_store_u32(SPEC == kSpecBF16 ? pack_bf16(X) : pack_f16(X), dst, o >> 1);
-        }
+        for (int j = 0; j < P1; ++j) w[j] = col_lds[k2 * (P1 + 1) + j];
+        dft<P1>(w);
+        static_for<P1>([&](auto K1) {
+          constexpr int k1 = decltype(K1)::value;
+          uint32_t o;
+          if constexpr (CACHE) o = at[q][k1]; else o = store_offset(q, k1);
+          float2 X = w[bitrev<P1>(k1)];
+          if constexpr (!REF) {
+            X.x *= scale;
+            X.y *= scale;
+          }
+          // Only output (q, k1) = (0, 0) of thread 0 of group 0 is k = 0.
+          if constexpr (q == 0 && k1 == 0) {
+            if (o == 0) X = make_float2(0.f, 0.f);
+          }
+          if constexpr (F32) {
+            buffer_store(X, dst, o);
+          } else {
+            // Offsets were computed for 8-byte modes; halving keeps the drop
+            // value out of range.
+            buffer_store_u32(SPEC == kSpecBF16 ? pack_bf16(X) : pack_f16(X), dst, o >> 1);
+          }
+        });
       });
-    });
+    };
+    if constexpr (FIRST && SPEC != kSpecF32) {
+      if (reference) second(std::true_type{}); else second(std::false_type{});
+    } else {
+      second(std::false_type{});
+    }
     if (++slot == capacity) slot = 0;
     __syncthreads();  // LDS is rewritten by the next frame
   }
@@ -487,11 +545,11 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
 template <int N, bool REF, int SPEC>
 __global__ __launch_bounds__(Col3Cfg<N>::THREADS, 4) void col3_pass_kernel(
     const float2* __restrict__ inter, const double* __restrict__ rowsum,
-    const double* __restrict__ rowabs, const double* __restrict__ refscal,
+    const double* __restrict__ rowabs, double* __restrict__ refscal,
     float4* __restrict__ fscale, int32_t* __restrict__ status, int nframes, int per_group,
     int64_t t0, int64_t capacity, int64_t mode_stride, int64_t n_modes,
     const int32_t* __restrict__ tiles, const float2* __restrict__ tw, char* __restrict__ ring,
-    float2* __restrict__ refspec, unsigned long long* __restrict__ work) {
+    float2* __restrict__ refspec, unsigned long long* __restrict__ work, int) {
   static_assert(!REF || SPEC == kSpecF32, "the reference transform is kept in FP32");
   constexpr bool F16 = SPEC == kSpecF16;
   constexpr uint32_t MODE_BYTES = SPEC == kSpecF32 ? 8u : 4u;
@@ -504,6 +562,7 @@ __global__ __launch_bounds__(Col3Cfg<N>::THREADS, 4) void col3_pass_kernel(
   __shared__ float2 twm[M];
   __shared__ double red[NWAVES];
   __shared__ double red_abs[F16 ? NWAVES : 1];
+  __shared__ double red_ref[REF ? 4 : 1];
 
   // Neighbouring column groups of a frame share an XCD (see col_pass_kernel).
   int bid = blockIdx.x;
@@ -533,6 +592,9 @@ __global__ __launch_bounds__(Col3Cfg<N>::THREADS, 4) void col3_pass_kernel(
   if constexpr (!REF) {
     s_ref = refscal[0];
     sigma_ref = refscal[1];
+  } else if (grp == 0 && f_begin == 0) {
+    const double total = reference_sum<N, THREADS>(rowsum, red_ref, tid);
+    if (tid == 0) write_reference_scale(total, reference_sigma(N, total), refscal, status);
   }
   float2* col = lds + c * CP;
   auto load_cols = [&](float2 (&v)[16], int f) {
@@ -1023,42 +1085,40 @@ __global__ __launch_bounds__(256, 2) void fused_transform_kernel(
 template <int N, typename T, bool WIN>
 hipError_t row_launch(const void* frames, const void* ref, const float* window, int nframes,
                       float2* inter, double* rowsum, double* rowabs, float* nyq,
-                      const float2* tw, hipStream_t s) {
+                      const float2* tw, void* ref_out, uint32_t* clear, hipStream_t s) {
   using C = RowCfg<N>;
-  const int per = frames_per_group(nframes, C::RB);
-  const int64_t blocks = int64_t(C::RB) * ((nframes + per - 1) / per);
-  if (rowabs) {
-    hipLaunchKernelGGL((row_pass_kernel<N, T, WIN, true>), dim3(unsigned(blocks)),
-                       dim3(C::THREADS), 0, s, static_cast<const T*>(frames),
-                       static_cast<const T*>(ref), window, nframes, per, inter, rowsum, rowabs,
-                       nyq, tw);
-  } else {
-    hipLaunchKernelGGL((row_pass_kernel<N, T, WIN, false>), dim3(unsigned(blocks)),
-                       dim3(C::THREADS), 0, s, static_cast<const T*>(frames),
-                       static_cast<const T*>(ref), window, nframes, per, inter, rowsum, rowabs,
-                       nyq, tw);
-  }
+  const int first = ref_out ? 1 : 0;
+  if (first && N > kFirstMax) return hipErrorInvalidValue;
+  const int per = frames_per_group(nframes + first, C::RB);
+  const int64_t blocks = int64_t(C::RB) * ((nframes + first + per - 1) / per);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(C::THREADS), 0, s,
+                       static_cast<const T*>(frames), static_cast<const T*>(ref), window,
+                       nframes, per, inter, rowsum, rowabs, nyq, tw, first,
+                       static_cast<T*>(ref_out), clear);
+  };
+  if (rowabs)
+    go(row_pass_kernel<N, T, WIN, true>);
+  else
+    go(row_pass_kernel<N, T, WIN, false>);
   return hipGetLastError();
 }
 
 template <int N>
 hipError_t row_dispatch(int in_dtype, const void* frames, const void* ref, const float* window,
                         int nframes, float2* inter, double* rowsum, double* rowabs, float* nyq,
-                        const float2* tw, hipStream_t s) {
-  if (in_dtype == 0) {
-    return window ? row_launch<N, uint16_t, true>(frames, ref, window, nframes, inter, rowsum,
-                                                  rowabs, nyq, tw, s)
-                  : row_launch<N, uint16_t, false>(frames, ref, window, nframes, inter, rowsum,
-                                                   rowabs, nyq, tw, s);
-  }
-  return window ? row_launch<N, float, true>(frames, ref, window, nframes, inter, rowsum,
-                                             rowabs, nyq, tw, s)
-                : row_launch<N, float, false>(frames, ref, window, nframes, inter, rowsum,
-                                              rowabs, nyq, tw, s);
+                        const float2* tw, void* ref_out, uint32_t* clear, hipStream_t s) {
+  auto go = [&](auto launch) {
+    return launch(frames, ref, window, nframes, inter, rowsum, rowabs, nyq, tw, ref_out, clear,
+                  s);
+  };
+  if (in_dtype == 0)
+    return window ? go(row_launch<N, uint16_t, true>) : go(row_launch<N, uint16_t, false>);
+  return window ? go(row_launch<N, float, true>) : go(row_launch<N, float, false>);
 }
 
 template <int N>
-hipError_t col_launch(bool reference, int spec, const float2* inter, const double* rowsum,
+hipError_t col_launch(ColFrames which, int spec, const float2* inter, const double* rowsum,
                       const double* rowabs, int nframes, int64_t t0, int64_t capacity,
                       int64_t mode_stride, int64_t n_modes, const int32_t* tiles,
                       const float2* tw, void* ring, float2* refspec,
@@ -1069,22 +1129,26 @@ hipError_t col_launch(bool reference, int spec, const float2* inter, const doubl
   // 128 threads and 40 KB of LDS (n = 512): four workgroups to a CU. A launch of
   // 128 frames takes 45.6 us with 1024 workgroups, 55.4 with 512; n = 1024 (256
   // threads, two to a CU) 44.7 with 512, 48.1 with 1024.
-  const int per = frames_per_group(nframes, C::GROUPS, threads < 256 ? 1024 : 512);
-  const int64_t blocks = int64_t(C::GROUPS) * ((nframes + per - 1) / per);
+  const int first = which == ColFrames::kFirst ? 1 : 0, total = nframes + first;
+  if (which == (N <= kFirstMax ? ColFrames::kReference : ColFrames::kFirst))
+    return hipErrorInvalidValue;
+  const int per = frames_per_group(total, C::GROUPS, threads < 256 ? 1024 : 512);
+  const int64_t blocks = int64_t(C::GROUPS) * ((total + per - 1) / per);
   char* ringb = static_cast<char*>(ring);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(threads), 0, s, inter, rowsum,
                        rowabs, refscal, fscale, status, nframes, per, t0, capacity, mode_stride,
-                       n_modes, tiles, tw, ringb, refspec, work);
+                       n_modes, tiles, tw, ringb, refspec, work, first);
   };
 #define NFS_COL_GO(REFV, SPECV)                        \
   if constexpr (N >= 2048)                             \
     go(col3_pass_kernel<N, REFV, SPECV>);              \
   else                                                 \
     go(col_pass_kernel<N, REFV, SPECV>)
-  if (reference) {
-    hipLaunchKernelGGL(ref_scale_kernel, dim3(1), dim3(256), 0, s, N, rowsum, refscal, status);
-    NFS_COL_GO(true, kSpecF32);
+  if (which == ColFrames::kReference) {
+    if constexpr (N > kFirstMax) {
+      NFS_COL_GO(true, kSpecF32);
+    }
   } else if (spec == kSpecBF16) {
     NFS_COL_GO(false, kSpecBF16);
   } else if (spec == kSpecF16) {
@@ -1100,11 +1164,12 @@ hipError_t col_launch(bool reference, int spec, const float2* inter, const doubl
 
 hipError_t launch_row_pass(int n, int in_dtype, const void* frames, const void* ref,
                            const float* window, int nframes, float2* inter, double* rowsum,
-                           double* rowabs, float* nyq, const float2* tw, hipStream_t s) {
+                           double* rowabs, float* nyq, const float2* tw, void* ref_out,
+                           uint32_t* clear, hipStream_t s) {
 #define NFS_ROW_CASE(NN)                                                                    \
   case NN:                                                                                  \
     return row_dispatch<NN>(in_dtype, frames, ref, window, nframes, inter, rowsum, rowabs, \
-                            nyq, tw, s);
+                            nyq, tw, ref_out, clear, s);
   switch (n) {
     NFS_ROW_CASE(16)
     NFS_ROW_CASE(32)
@@ -1178,7 +1243,7 @@ hipError_t launch_nyquist_col(int n, bool reference, int spec, const float* nyq,
   return hipGetLastError();
 }
 
-hipError_t launch_col_pass(int n, bool reference, int spec, const float2* inter,
+hipError_t launch_col_pass(int n, ColFrames which, int spec, const float2* inter,
                            const double* rowsum, const double* rowabs, int nframes, int64_t t0,
                            int64_t capacity, int64_t mode_stride, int64_t n_modes,
                            const int32_t* tiles, const float2* tw, void* ring,
@@ -1186,7 +1251,7 @@ hipError_t launch_col_pass(int n, bool reference, int spec, const float2* inter,
                            unsigned long long* work, hipStream_t s) {
 #define NFS_COL_CASE(NN)                                                                   \
   case NN:                                                                                 \
-    return col_launch<NN>(reference, spec, inter, rowsum, rowabs, nframes, t0, capacity,  \
+    return col_launch<NN>(which, spec, inter, rowsum, rowabs, nframes, t0, capacity,  \
                           mode_stride, n_modes, tiles, tw, ring, refspec,                 \
                           refscal, fscale, status, work, s);
   switch (n) {

@@ -58,6 +58,7 @@ struct nfs_plan_s {
   int64_t t_done = 0;    // frames whose pairs (as the later frame) are summed
   // No pair launch since the sums were reset: the next one stores its sums
   // instead of adding them, so a reset needs no fill of the sums.
+  bool clear_due = false;       // the status block is to be cleared before its next use
   bool sums_fresh = true;
   // Host pushes (host_staging): two device staging buffers of one batch;
   // copies run on `copy`, transforms on `stream`. copied[j] marks batch
@@ -200,10 +201,13 @@ nfs_status flush_pairs(nfs_plan_s* h) {
   return NFS_OK;
 }
 
+nfs_status settle_clear(nfs_plan_s* h);
+
 // Sums ready for reading: pending pairs summed, and zeros where no pair
 // launch has run since the reset (no frames pushed).
 nfs_status finish_sums(nfs_plan_s* h) {
-  nfs_status st = flush_pairs(h);
+  nfs_status st = settle_clear(h);
+  if (st == NFS_OK) st = flush_pairs(h);
   if (st != NFS_OK || !h->sums_fresh) return st;
   const nfs::Layout& L = h->L;
   hipError_t e = nfs::launch_fill_u32(h->acc, size_t(L.n_lags) * L.mode_stride, 0u, h->stream);
@@ -214,14 +218,28 @@ nfs_status finish_sums(nfs_plan_s* h) {
   return NFS_OK;
 }
 
-nfs_status clear_sums(nfs_plan_s* h) {
-  // The status word, the reference scalars (rewritten by the next push) and
-  // the work counters: the first 80 bytes of the status block.
-  hipError_t e = nfs::launch_fill_u32(h->status, 20, 0u, h->stream);
+// The status word, the reference scalars (rewritten by the next push) and the
+// work counters, the first words of the status block, are cleared by the first
+// batch's row pass where that takes the reference along, else by a kernel of
+// their own before the next use.
+nfs_status settle_clear(nfs_plan_s* h) {
+  if (!h->clear_due) return NFS_OK;
+  hipError_t e = nfs::launch_fill_u32(h->status, nfs::kClearWords, 0u, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "fill kernel launch");
+  h->clear_due = false;
+  return NFS_OK;
+}
+
+nfs_status clear_sums(nfs_plan_s* h) {
+  h->clear_due = true;
   h->sums_fresh = true;
   h->t_pushed = 0;
   h->t_done = 0;
+  // Recorded into a graph, a reset clears whenever the graph runs.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess ||
+      capture != hipStreamCaptureStatusNone)
+    return settle_clear(h);
   return NFS_OK;
 }
 
@@ -232,10 +250,11 @@ struct BatchScratch {
   double* rowsum;
   double* rowabs;
   float* nyq;
+  int64_t frames;  // it holds
 };
 
 BatchScratch plan_scratch(const nfs_plan_s* h) {
-  return {h->inter, h->rowsum, h->rowabs, h->nyq};
+  return {h->inter, h->rowsum, h->rowabs, h->nyq, h->L.batch};
 }
 
 // Scratch of b frames laid out from `base` on, and its size.
@@ -251,6 +270,7 @@ size_t scratch_layout(const nfs_plan_s* h, int64_t b, char* base, BatchScratch* 
   out->rowsum = reinterpret_cast<double*>(take(size_t(b) * L.n * 8));
   out->rowabs = h->rowabs ? reinterpret_cast<double*>(take(size_t(b) * L.n * 8)) : nullptr;
   out->nyq = h->nyq ? reinterpret_cast<float*>(take(size_t(b) * L.n * 4)) : nullptr;
+  out->frames = b;
   return off;
 }
 
@@ -274,13 +294,17 @@ int64_t next_batch(const nfs_plan_s* h, int64_t left, BatchScratch* scratch) {
   const nfs::Layout& L = h->L;
   *scratch = plan_scratch(h);
   int64_t best = next_batch(h, left);
+  // A sequence's first batch leaves room for the reference (see transform_batch)
+  // if that costs it little.
+  const int extra = h->t_pushed == 0 && L.n <= nfs::kFirstMax ? 1 : 0;
+  if (extra && best == L.batch && best >= 8) --best;
   const int64_t free_slots = L.capacity - h->t_pushed;
   const size_t frame = size_t(L.n) * L.h * 8;
   const int64_t want = std::min({left, free_slots, int64_t(nfs::kMaxBatch),
                                  std::max<int64_t>(1, int64_t(nfs::kBatchBytes / frame))});
   auto fits = [&](int64_t b, char* base, size_t room) {
     BatchScratch t;
-    return scratch_layout(h, b, base, &t) <= room;
+    return scratch_layout(h, b + extra, base, &t) <= room;
   };
   auto consider = [&](auto&& base_of, auto&& room_of) {
     int64_t lo = best, hi = want;  // the largest b in (best, want] that fits, by bisection
@@ -290,7 +314,7 @@ int64_t next_batch(const nfs_plan_s* h, int64_t left, BatchScratch* scratch) {
     }
     if (lo > best) {
       best = lo;
-      scratch_layout(h, lo, base_of(lo), scratch);
+      scratch_layout(h, lo + extra, base_of(lo), scratch);
     }
   };
   if (h->fused) return best;
@@ -344,11 +368,13 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
     return NFS_OK;
   }
   hipError_t e = nfs::launch_row_pass(L.n, L.in_dtype, src, h->ref, h->window, int(b),
-                                      w.inter, w.rowsum, w.rowabs, w.nyq, h->tw, h->stream);
+                                      w.inter, w.rowsum, w.rowabs, w.nyq, h->tw, nullptr,
+                                      nullptr, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "row pass launch");
-  e = nfs::launch_col_pass(L.n, false, L.spec_dtype, w.inter, w.rowsum, w.rowabs, int(b), t,
-                           L.capacity, L.mode_stride, L.slots, h->tiles, h->tw, h->ring,
-                           h->refspec, h->refscal, h->fscale, h->status, h->work, h->stream);
+  e = nfs::launch_col_pass(L.n, nfs::ColFrames::kFrames, L.spec_dtype, w.inter, w.rowsum,
+                           w.rowabs, int(b), t, L.capacity, L.mode_stride, L.slots, h->tiles,
+                           h->tw, h->ring, h->refspec, h->refscal, h->fscale, h->status, h->work,
+                           h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "column pass launch");
   if (L.full) {
     e = nfs::launch_nyquist_col(L.n, false, L.spec_dtype, w.nyq, int(b), t, L.capacity,
@@ -359,30 +385,70 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
   return NFS_OK;
 }
 
+// The reference of frames above kFirstMax, by itself.
+nfs_status reference_batch(nfs_plan_s* h, const char* src) {
+  const nfs::Layout& L = h->L;
+  nfs_status st = settle_clear(h);
+  if (st != NFS_OK) return st;
+  hipError_t e = hipMemcpyAsync(h->ref, src, L.frame_bytes, hipMemcpyDeviceToDevice, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "reference copy");
+  e = nfs::launch_row_pass(L.n, L.in_dtype, h->ref, nullptr, h->window, 1, h->inter, h->rowsum,
+                           nullptr, h->nyq, h->tw, nullptr, nullptr, h->stream);
+  if (e == hipSuccess)
+    e = nfs::launch_col_pass(L.n, nfs::ColFrames::kReference, NFS_SPEC_F32, h->inter, h->rowsum,
+                             nullptr, 1, 0, L.capacity, L.mode_stride, L.slots, h->tiles, h->tw,
+                             h->ring, h->refspec, h->refscal, h->fscale, h->status, nullptr,
+                             h->stream);
+  if (e == hipSuccess && L.full)
+    e = nfs::launch_nyquist_col(L.n, true, NFS_SPEC_F32, h->nyq, 1, 0, L.capacity,
+                                L.mode_stride, L.nyq_slot, h->tw, h->fscale, h->ring, h->refspec,
+                                h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "reference transform launch");
+  return NFS_OK;
+}
+
+// The first `b` frames of a sequence (none for b = 0) with its reference, in the
+// launches of one batch. Scratch of b + 1 frames.
+nfs_status first_batch(nfs_plan_s* h, const char* src, int64_t b, const BatchScratch& w) {
+  const nfs::Layout& L = h->L;
+  uint32_t* clear = h->clear_due ? reinterpret_cast<uint32_t*>(h->status) : nullptr;
+  hipError_t e = nfs::launch_row_pass(L.n, L.in_dtype, src, src, h->window, int(b), w.inter,
+                                      w.rowsum, w.rowabs, w.nyq, h->tw, h->ref, clear, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "row pass launch");
+  h->clear_due = false;
+  e = nfs::launch_col_pass(L.n, nfs::ColFrames::kFirst, L.spec_dtype, w.inter, w.rowsum,
+                           w.rowabs, int(b), 0, L.capacity, L.mode_stride, L.slots, h->tiles,
+                           h->tw, h->ring, h->refspec, h->refscal, h->fscale, h->status, h->work,
+                           h->stream);
+  if (e == hipSuccess && L.full)
+    e = nfs::launch_nyquist_col(L.n, false, L.spec_dtype, w.nyq, int(b), 0, L.capacity,
+                                L.mode_stride, L.nyq_slot, h->tw, h->fscale, h->ring, h->refspec,
+                                h->stream);
+  if (e == hipSuccess && L.full)
+    e = nfs::launch_nyquist_col(L.n, true, NFS_SPEC_F32, w.nyq + size_t(b) * L.n, 1, 0,
+                                L.capacity, L.mode_stride, L.nyq_slot, h->tw, h->fscale, h->ring,
+                                h->refspec, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "first batch launch");
+  h->t_pushed += b;
+  return NFS_OK;
+}
+
 // Normalise, transform and store `b` frames (device memory, as many as the
 // scratch holds) as frames [t_pushed, t_pushed + b); make_room must precede it.
 nfs_status transform_batch(nfs_plan_s* h, const char* src, int64_t b, const BatchScratch& w) {
   const nfs::Layout& L = h->L;
-  hipError_t e = hipSuccess;
   if (h->t_pushed == 0) {
     // The first frame of the sequence becomes the reference subtracted
     // from every frame before its transform; differences of transforms
     // are unchanged, but the stored values no longer carry the static
     // image, whose low-q coefficients would swamp FP32.
-    e = hipMemcpyAsync(h->ref, src, L.frame_bytes, hipMemcpyDeviceToDevice, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "reference copy");
-    e = nfs::launch_row_pass(L.n, L.in_dtype, h->ref, nullptr, h->window, 1, h->inter,
-                             h->rowsum, nullptr, h->nyq, h->tw, h->stream);
-    if (e == hipSuccess)
-      e = nfs::launch_col_pass(L.n, true, NFS_SPEC_F32, h->inter, h->rowsum, nullptr, 1, 0,
-                               L.capacity, L.mode_stride, L.slots, h->tiles, h->tw,
-                               h->ring, h->refspec, h->refscal, h->fscale, h->status,
-                               nullptr, h->stream);
-    if (e == hipSuccess && L.full)
-      e = nfs::launch_nyquist_col(L.n, true, NFS_SPEC_F32, h->nyq, 1, 0, L.capacity,
-                                  L.mode_stride, L.nyq_slot, h->tw, h->fscale, h->ring,
-                                  h->refspec, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "reference transform launch");
+    if (L.n <= nfs::kFirstMax) {
+      const bool along = b + 1 <= w.frames;
+      nfs_status st = first_batch(h, src, along ? b : 0, along ? w : plan_scratch(h));
+      if (st != NFS_OK || along) return st;
+    } else if (nfs_status st = reference_batch(h, src); st != NFS_OK) {
+      return st;
+    }
   }
   nfs_status st = transform_into_ring(h, src, b, h->t_pushed, w);
   if (st != NFS_OK) return st;
@@ -831,6 +897,8 @@ nfs_status nfs_structure_function_noalloc(const nfs_desc* desc, const void* fram
 nfs_status nfs_work_counters(nfs_handle h, int64_t* counters) {
   if (!is_live(h)) return NFS_E_STATE;
   if (!counters) return fail(h, NFS_E_ARG, "counters is NULL");
+  nfs_status st = settle_clear(h);
+  if (st != NFS_OK) return st;
   hipError_t e = hipMemcpyAsync(counters, h->work, 2 * sizeof(int64_t),
                                 hipMemcpyDeviceToDevice, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "work counter copy");

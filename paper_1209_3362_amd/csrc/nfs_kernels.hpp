@@ -21,9 +21,16 @@ namespace nfs {
 // when rowabs is not null, rowabs [nframes][n]: the rows' sums of |what was
 // transformed|.
 // nyq: [nframes][n] floats receiving X_y(n/2) (full half-plane plans), or null.
+// ref_out (n <= kFirstMax, ref == frames): the batch starts a sequence; its frame
+// 0, nothing subtracted, is transformed as one more frame (every output then
+// holds nframes + 1; nframes may be 0) and copied there, and kClearWords words at
+// `clear` (or null) are set to 0.
+constexpr int kFirstMax = 512;
+constexpr int kClearWords = 20;
 hipError_t launch_row_pass(int n, int in_dtype, const void* frames, const void* ref,
                            const float* window, int nframes, float2* inter, double* rowsum,
-                           double* rowabs, float* nyq, const float2* tw, hipStream_t s);
+                           double* rowabs, float* nyq, const float2* tw, void* ref_out,
+                           uint32_t* clear, hipStream_t s);
 
 // Fused row and column passes of `nframes` frames (n = 1024 only) in one
 // persistent launch of `workers` workgroups: per-XCD task queues, the
@@ -55,10 +62,12 @@ hipError_t launch_nyquist_col(int n, bool reference, int spec, const float* nyq,
 
 // Column pass (per column k_x: complex transform over the n rows), with the
 // frame scales formed from the row sums.
-// reference == true: the rows are the reference image (one frame); set
-// refscal = {S_ref, n^2/S_ref} and store its transform unscaled in refspec
-// (FP32, 0 at k = 0).
-// reference == false: the rows are (frame - reference); with
+// kReference (n > kFirstMax): the rows are the reference image; set refscal =
+// {S_ref, n^2/S_ref} and store its transform unscaled in refspec (FP32, 0 at
+// k = 0).
+// kFirst (n <= kFirstMax): as kFrames for `nframes` frames and as kReference for
+// one more after them (see launch_row_pass, ref_out).
+// kFrames: the rows are (frame - reference); with
 // sigma = n^2 / (S_ref + row sums), store sigma * X, 0 at k = 0, for frame f
 // in ring slot slot = (t0 + f) mod capacity in the storage type `spec`
 // (nfs_desc.spec_dtype: 8 or 4 bytes per mode, mode_stride modes per slot),
@@ -67,7 +76,8 @@ hipError_t launch_nyquist_col(int n, bool reference, int spec, const float* nyq,
 // is not positive and finite sets bit 0 of *status and gets sigma = 0.
 // n_modes: slots per spectrum in the tiled layout (tiles, see ring_slot);
 // only those are written.
-hipError_t launch_col_pass(int n, bool reference, int spec, const float2* inter,
+enum class ColFrames { kFrames, kReference, kFirst };
+hipError_t launch_col_pass(int n, ColFrames which, int spec, const float2* inter,
                            const double* rowsum, const double* rowabs, int nframes, int64_t t0,
                            int64_t capacity, int64_t mode_stride, int64_t n_modes,
                            const int32_t* tiles, const float2* tw, void* ring,

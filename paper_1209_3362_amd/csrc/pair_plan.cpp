@@ -105,6 +105,9 @@ std::vector<LagGroup> group_candidates(const std::vector<int32_t>& lags, int fir
 // frames 51 / 57) and any number where the history leaves the other kernel one
 // workgroup per CU (5 lags up to 300 over 600 frames 251 / 160). From 640 frames
 // on two workgroups no longer fit a CU: 900 and 16 387 / 538.
+// Frames of up to 128 x 128 have fewer workgroups than the chip holds, so the
+// waves of one decide: 31 lags over 64 frames of 128 x 128 10 / 14 (10 with 8
+// waves), of 256 x 256 25 / 19.
 // 32 modes per workgroup read rows in pieces of 256 bytes and waste fewer masked
 // targets, as long as four workgroups fit a CU: 64 frames and 32 lags 50 / 72
 // us with 32 / 16 modes, 192 frames and 32 lags 198 / 132; with few lags the
@@ -113,7 +116,7 @@ std::vector<LagGroup> group_candidates(const std::vector<int32_t>& lags, int fir
 // 16 lags 182 / 261 with 8 / 4, 192 frames 109 / 95.
 bool window_shape(const LagGroup& group, int64_t n_modes, int64_t T0, int64_t T1,
                   WindowShape* w) {
-  if (group.modes == 0) return false;
+  if (group.modes == 0 || n_modes < 64 * kCus) return false;
   const int count = group.count;
   w->n_lags = count;
   w->pre = int(std::min<int64_t>(group.max_lag, T0));
