@@ -70,7 +70,7 @@ nfs_status validate_desc(const nfs_desc* d, std::string* err) {
 }
 
 nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
-                       std::string* err) {
+                       std::string* err, bool sizes_only) {
   nfs_status st = validate_desc(d, err);
   if (st != NFS_OK) return st;
   Layout& o = *L;
@@ -135,32 +135,34 @@ nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
   // Binning table and segments, rings in order. On row k_y the half-plane
   // modes of ring b are the run k_x in [ceil_sqrt(lo - k_y^2),
   // ceil_sqrt(hi - k_y^2)); every one of them is stored (|k| < n/2).
-  o.bin_slots.reserve(size_t(o.binned));
+  const size_t ring_modes = size_t(o.binned);
+  if (!sizes_only) o.bin_slots.reserve(ring_modes);
   o.bin_seg0.push_back(0);
+  int32_t last = 0;
   for (int b = 0; b < o.n_bins; ++b) {
     int64_t lo, hi;
     ring_bounds(o.n, o.n_bins, b, &lo, &hi);
     const int R = int(isqrt_u64(uint64_t(hi - 1)));
-    const int32_t first = int32_t(o.bin_slots.size());
+    int32_t s = last;
     for (int ky = -R; ky <= R; ++ky) {
       const int64_t ky2 = int64_t(ky) * ky;
       const int a = lo - ky2 > 0 ? int(ceil_sqrt_i64(lo - ky2)) : 0;
       const int e = int(ceil_sqrt_i64(hi - ky2));
       const int r = ky >= 0 ? ky : ky + o.n;
+      last += std::max(0, e - a);
+      if (sizes_only) continue;
       for (int kx = a; kx < e; ++kx)
         o.bin_slots.push_back(2 * ring_slot_host(o, r, kx) + (kx > 0 ? 1 : 0));
     }
-    const int32_t last = int32_t(o.bin_slots.size());
-    int32_t s = first;
     do {
       o.seg_first.push_back(s);
       s += kSegModes;
     } while (s < last);
     o.bin_seg0.push_back(int32_t(o.seg_first.size()));
   }
-  o.seg_first.push_back(int32_t(o.bin_slots.size()));
+  o.seg_first.push_back(last);
   // The rings partition the modes with |k| < n/2: each is listed exactly once.
-  {
+  if (!sizes_only) {
     std::vector<char> seen(size_t(o.slots), 0);
     bool ok = int64_t(o.bin_slots.size()) == o.binned;
     for (size_t i = 0; ok && i < o.bin_slots.size(); ++i) {
@@ -222,8 +224,10 @@ nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
   o.fused_slots = (o.batch + 7) / 8;  // frames per XCD per launch at most
   o.off_sched = take(o.fused_ok ? size_t(8 * 64 + 16 * o.fused_slots) * 4 : 0);
   const size_t nseg = o.seg_first.size() - 1;
+  // Tables in three runs of neighbours, each one upload: segs and bin_slots, tw to
+  // lags, mode_bin and bin_count.
   o.off_segs = take((o.seg_first.size() + o.bin_seg0.size()) * 4);
-  o.off_bin_slots = take(o.bin_slots.size() * 4);
+  o.off_bin_slots = take(ring_modes * 4);
   o.off_part = take(nseg * o.n_lags * 8);
   o.off_part_cnt = take(nseg * 8);
   o.off_status = take(kAlign);
@@ -245,17 +249,16 @@ nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
     // Bin of every stored mode and C_b, the full-plane modes of each bin:
     // a half-plane mode with k_x > 0 stands for itself and its mirror.
     // Slots of modes that are not stored get -1 (no gradient).
-    o.mode_bin.assign(size_t(o.mode_stride), -1);
-    o.bin_count.assign(size_t(o.n_bins), 0);
-    const uint64_t nb2 = uint64_t(o.n_bins) * uint64_t(o.n_bins);
-    for (int r = 0; r < o.n; ++r) {
-      const int64_t ky = r < o.h ? r : r - o.n;
-      for (int kx = 0; kx < disc[size_t(r)]; ++kx) {
-        const uint64_t k2 = uint64_t(ky * ky) + uint64_t(kx) * uint64_t(kx);
-        const int b = int(isqrt_u64(k2 * nb2) / uint64_t(o.h));
-        o.mode_bin[size_t(ring_slot_host(o, r, kx))] = b;
-        o.bin_count[size_t(b)] += kx == 0 ? 1 : 2;
-      }
+    if (!sizes_only) {
+      o.mode_bin.assign(size_t(o.mode_stride), -1);
+      o.bin_count.assign(size_t(o.n_bins), 0);
+      for (int b = 0; b < o.n_bins; ++b)
+        for (int32_t i = o.seg_first[size_t(o.bin_seg0[size_t(b)])];
+             i < o.seg_first[size_t(o.bin_seg0[size_t(b) + 1])]; ++i) {
+          const int32_t code = o.bin_slots[size_t(i)];
+          o.mode_bin[size_t(code >> 1)] = b;
+          o.bin_count[size_t(b)] += 1 + (code & 1);
+        }
     }
   }
   o.off_refspec = take(size_t(o.mode_stride) * 8);

@@ -105,8 +105,9 @@ nfs_status validate_desc(const nfs_desc* d, std::string* err);
 // Builds the layout for `d`. With d->capacity == 0 and bytes_available > 0,
 // the ring takes every whole spectrum that fits; with both 0 the ring has
 // max_lag + 64 slots.
+// sizes_only: every size and offset, but none of the tables (segments apart).
 nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
-                       std::string* err);
+                       std::string* err, bool sizes_only = false);
 
 // Host twin of the device ring_slot: slot of (row r, column kx) in the
 // tiled layout, or -1 when the row is not kept in kx's tile.
