@@ -238,9 +238,11 @@ nfs_status clear_sums(nfs_plan_s* h) {
   h->t_done = 0;
   // Recorded into a graph, a reset clears whenever the graph runs.
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess ||
-      capture != hipStreamCaptureStatusNone)
+  if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();  // the launches report their own
     return settle_clear(h);
+  }
+  if (capture != hipStreamCaptureStatusNone) return settle_clear(h);
   return NFS_OK;
 }
 
