@@ -13,7 +13,7 @@
 // each wave takes 64 table entries (one per lane), then walks them with the
 // lags on LG = 8, 16, 32 or 64 lanes and 64 / LG entries side by side, eight
 // reads in flight; the entries' sums meet by shuffles and in LDS. Where every
-// ring is one segment (up to kSegModes modes: n <= 160 with rings of width 1)
+// ring is one segment (up to kSegModes modes: n <= 128 with rings of width 1)
 // that is its sum; elsewhere a second kernel adds the segments of each ring in
 // order. (A workgroup for each ring of any size leaves the chip idle: 23
 // against 13 + 5 us with rings of up to 402 modes, 32 lags; 68 against 40 + 5
