@@ -133,6 +133,13 @@ void mx_workgroup(MxShape* s, int64_t modes) {
   s->lds = lds(km);
 }
 
+bool mx_direct(const MxShape& s, int64_t capacity, int64_t row) {
+  // Offsets go from -tbase rows (modulo 2^32) to fewer than pl rows, and a range
+  // and its places before its first frame are within pl rows.
+  return s.olo % capacity + s.olen <= capacity && s.t0 % capacity + (s.t1 - s.t0) <= capacity &&
+         int64_t(s.pl) * row <= int64_t(1) << 32;
+}
+
 void mx_tables(const std::vector<int32_t>& lags, const MxGroup& g, int64_t t0, int64_t t1,
                MxTables* out) {
   MxTables& o = *out;

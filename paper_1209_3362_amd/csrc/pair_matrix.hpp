@@ -120,6 +120,12 @@ int64_t mx_cut(int64_t t0, int64_t t1, int64_t ta, int64_t tb);
 // Modes per workgroup and LDS bytes of a shape for `modes` modes.
 void mx_workgroup(MxShape* s, int64_t modes);
 
+// Whether the kernel may read rows of `row` bytes by 32-bit offsets from the
+// first row of each range: neither range wraps in the ring, and no place of the
+// plane is 4 GiB or more from it. Places that are no frame's, up to 207 past the
+// last one, then lie past the range's descriptor and read as 0.
+bool mx_direct(const MxShape& s, int64_t capacity, int64_t row);
+
 // Tables for the group's delays below t1 and the targets [t0, t1).
 void mx_tables(const std::vector<int32_t>& lags, const MxGroup& g, int64_t t0, int64_t t1,
                MxTables* out);

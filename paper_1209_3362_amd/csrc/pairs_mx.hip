@@ -61,7 +61,7 @@ struct MxArgs {
   int64_t olo;
   int32_t n_lags, acc_pitch, assign;
   int32_t zero_from;  // delays from this one on have no pair: set to 0 with `assign`
-  int32_t direct;     // no range wraps in the ring or passes 4 GB: buffer loads
+  int32_t direct;     // buffer loads (see mx_direct)
   MxTables tab;
 };
 
@@ -789,10 +789,7 @@ hipError_t launch_pairs_mx(const void* ring, int spec, const float2* refspec,
   a.acc_pitch = acc_pitch;
   a.assign = assign;
   a.zero_from = tab.n_paired;
-  const int64_t row = mode_stride * (spec == kSpecF32 ? 8 : 4);
-  const int64_t rows = std::max(int64_t(s.olen), s.t1 - s.t0) + 64;
-  a.direct = a.slot_old + int64_t(s.olen) <= capacity &&
-             a.slot_new + (s.t1 - s.t0) <= capacity && rows * row < (int64_t(1) << 32);
+  a.direct = mx_direct(s, capacity, mode_stride * (spec == kSpecF32 ? 8 : 4));
   a.tab = tab;
   const int64_t blocks = ((n_modes + s.km - 1) / s.km + 7) / 8 * 8;
 #define NFS_MX_GO(SPECV)                                                                        \
