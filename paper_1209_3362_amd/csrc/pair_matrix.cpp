@@ -123,7 +123,8 @@ int64_t mx_cut(int64_t t0, int64_t t1, int64_t ta, int64_t tb) {
 
 void mx_workgroup(MxShape* s, int64_t modes) {
   auto lds = [&](int km) {
-    return size_t(km) * (9 * size_t(s->pl) + kMxRounds * kMxWaves * 8 + kMxWaves * 4) + 16;
+    return size_t(km) * (9 * size_t(s->pl) + kMxRounds * kMxWaves * 8 + kMxWaves * 4 +
+                         kMxLags / 8) + 16;
   };
   int km = 16;
   // As many modes as two workgroups per CU leave LDS for, fewer while the

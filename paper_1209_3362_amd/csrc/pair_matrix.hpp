@@ -39,6 +39,11 @@ constexpr int kMxRounds = 5;  // of octets that a thread loads at most
 constexpr int kMxPlane = 2240;
 // LDS of one workgroup, half a CU's.
 constexpr int kMxLds = 80 * 1024;
+// Sums below this many steps^2 of a mode's whole numbers are formed again from
+// its coefficients. Rounding them moves a sum of P pairs by 0.82 / sqrt(S) of
+// itself (rms; at most 2.9 sqrt(P / S)): 2^-24 at the line, the rounding of one
+// FP32 term.
+constexpr unsigned long long kMxLeast = 1ull << 48;
 // Delays of one launch span at most this many frames when a window has to be
 // cut, so that its two frame ranges leave room for targets.
 constexpr int kMxSpan = 600;

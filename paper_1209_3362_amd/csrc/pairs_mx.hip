@@ -6,7 +6,10 @@
 // (FP32 keeps 24 bits, so the largest are kept exactly) and all sums are
 // exact modulo 2^64, which holds S_tau itself (2 * 2^52 * pairs < 2^64). So
 // nothing cancels: equal frames give exactly 0, and the only rounding is
-// that of the coefficients, at most 2^-26 of the mode's largest.
+// that of the coefficients, at most 2^-26 of the mode's largest. A sum that this
+// rounding reaches is summed again from the coefficients themselves: below
+// kMxLeast steps^2 (few pairs, slow modes, or one frame far larger than the
+// others), and all sums of a mode with a value that is not finite.
 //
 // The cross terms are byte products on MFMA (see pair_matrix.hpp): a
 // 16 x 16 x 64 product gives 16 delays over 64 frames with all 16 digit
@@ -276,8 +279,11 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   const int lds0 = lds_address(smem);
   auto* tot = reinterpret_cast<unsigned long long*>(smem + km * mode_lds);  // [rounds][waves][km]
   auto* top = reinterpret_cast<unsigned*>(tot + ROUNDS * kMxWaves * km);     // [waves][km]
-  auto* odd_flag = top + kMxWaves * km;  // some value of the workgroup is not finite
-  if (tid == 0) *odd_flag = 0;
+  // marks[0]: some value of the workgroup is not finite, [1]: some sum is small;
+  // small: its sums that are, a bit per mode and delay index.
+  auto* marks = top + kMxWaves * km;
+  auto* small = marks + 2;
+  for (int e = tid; e < 2 + kMxLags / 32 * km; e += THREADS) marks[e] = 0;
 
   // Workgroups are dispatched round robin over the 8 XCDs; neighbouring
   // workgroups, whose modes share lines of the ring, stay on one XCD's L2.
@@ -428,37 +434,25 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   unsigned big = __float_as_uint(largest_abs) & 0x7fffffffu;  // as bits, in order
   for (int o = km; o < 64; o <<= 1) big = max(big, unsigned(__shfl_xor(int(big), o, 64)));
   if (lane < km) top[wave * km + lane] = big;
-  if (big >= 0x7f800000u) *odd_flag = 1;
+  if (big >= 0x7f800000u) marks[0] = 1;
   __syncthreads();
 
-  // Scale 2^exp[mode] to at most 2^25 for the mode's largest number. Values
-  // that are not finite become 0 here and are dealt with at the end: bit 31
-  // of `top` marks their modes.
-  constexpr unsigned kOdd = 0x80000000u;
+  // Scale 2^exponent to at most 2^25 for the mode's largest number. A mode with a
+  // value that is not finite becomes 0 here: all its sums are small.
   auto largest = [&](int mode) -> unsigned {
     unsigned b = 0;
 #pragma unroll
     for (int w = 0; w < kMxWaves; ++w) b = max(b, top[w * km + mode]);
     return b;
   };
-  if (*odd_flag) {
-    const bool odd = largest(lm) >= 0x7f800000u;
-    big = 0;
+  if (marks[0] && largest(lm) >= 0x7f800000u) {
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (!isfinite(v[r][i].x)) v[r][i].x = 0.f;
-        if (!isfinite(v[r][i].y)) v[r][i].y = 0.f;
-        big = max(big, max(__float_as_uint(fabsf(v[r][i].x)), __float_as_uint(fabsf(v[r][i].y))));
-      }
-    for (int o = km; o < 64; o <<= 1) big = max(big, unsigned(__shfl_xor(int(big), o, 64)));
-    __syncthreads();  // every thread has read the marks
-    if (lane < km) top[wave * km + lane] = big | (odd ? kOdd : 0u);
-    __syncthreads();
+      for (int i = 0; i < 8; ++i) v[r][i] = make_float2(0.f, 0.f);
   }
   auto exponent = [](unsigned b) -> int {
-    const int e = int((b & ~kOdd) >> 23);
+    const int e = int(b >> 23);
     return 25 - ((e < 1 ? 1 : e) - 126);
   };
   const int ex = exponent(largest(lm));
@@ -530,6 +524,26 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   }
   __syncthreads();
 
+  // A window's sum of delay index l into the running sum.
+  auto add_sum = [&](int64_t mode, int l, float val) {
+    float* sum = a.acc + mode * a.acc_pitch + l;
+    if (a.comp) {
+      float* comp = a.comp + mode * a.acc_pitch + l;
+      if (a.assign) {
+        *sum = val;
+        *comp = 0.f;
+      } else {
+        const float was = *sum;
+        const float y = val - *comp;
+        const float t = was + y;
+        *comp = (t - was) - y;
+        *sum = t;
+      }
+    } else {
+      *sum = a.assign ? val : *sum + val;
+    }
+  };
+
   // ---- products: waves take modes, and tasks when there are more waves ----
   const int tn = int(a.t1 - a.t0);
   const int share = km < kMxWaves ? kMxWaves / km : 1;
@@ -553,8 +567,6 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       const char* planes = smem + mm * mode_lds;
       const int back = -2 * exponent(largest(mm));
       const bool stored = m0 + mm < a.n_modes;
-      float* acc_m = a.acc + (m0 + mm) * a.acc_pitch;
-      float* comp_m = a.comp ? a.comp + (m0 + mm) * a.acc_pitch : nullptr;
 
       // Energies of a delay: targets [from, t1) and older frames [from - tau,
       // t1 - tau), from = max(t0, tau). The prefix at t1 is the total; that at
@@ -562,24 +574,16 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       const unsigned long long total = prefix_at(planes, pl, pl - 8);
       unsigned long long at_t0 = 0;
       if (a.t0 > 0) at_t0 = prefix_at(planes, pl, a.tbase);
-      // S of delay index l into the running sums.
+      // S of delay index l into the running sums, or to the small ones. A mode
+      // of zeros has no small sums.
+      const unsigned long long least = largest(mm) ? kMxLeast : 0;
       auto put = [&](int l, unsigned long long S) {
-        const float val = float(ldexp(double(S), back));
-        if (comp_m) {
-          // Window totals into the running sum with Kahan compensation.
-          if (a.assign) {
-            acc_m[l] = val;
-            comp_m[l] = 0.f;
-          } else {
-            const float was = acc_m[l];
-            const float y = val - comp_m[l];
-            const float t = was + y;
-            comp_m[l] = (t - was) - y;
-            acc_m[l] = t;
-          }
-        } else {
-          acc_m[l] = a.assign ? val : acc_m[l] + val;
+        if (S < least) {
+          atomicOr(&small[mm * (kMxLags / 32) + (l >> 5)], 1u << (l & 31));
+          marks[1] = 1;
+          return;
         }
+        add_sum(m0 + mm, l, float(ldexp(double(S), back)));
       };
       // Four tiles' sums (lane: delay place lane / 4, target digit lane % 4) to
       // cross sums modulo 2^64: class lane % 4 of place lane / 4.
@@ -694,58 +698,43 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
     }
   }
 
-  // ---- values that are not finite: their pairs, explicitly ----
-  if (!*odd_flag) return;
-  __threadfence();
+  // ---- small sums, explicitly: the coefficients take the planes' room, a wave
+  // a mode's delays on its lanes, FP32 terms into an FP64 sum ----
+  __syncthreads();
+  if (!marks[1]) return;
+  for (int oct = oct0; oct < octets; oct += step)
+    for (int i = 0; i < 8; ++i) {
+      const int slot = slot_at(8 * oct + i);
+      const float4 f = a.fscale[max(slot, 0)];
+      const Word w = *reinterpret_cast<const Word*>(ring_m + max(slot, 0) * slot_bytes);
+      reinterpret_cast<float2*>(planes_m)[8 * oct + i] =
+          slot >= 0 ? decode(w, f.y, f.z, R) : make_float2(0.f, 0.f);
+    }
   __syncthreads();
   for (int mm = wave; mm < km; mm += kMxWaves) {
-    if (m0 + mm >= a.n_modes || !(largest(mm) & kOdd)) continue;
-    const char* base = a.ring + (m0 + mm) * MODE_BYTES;
-    const float2 ref = a.refspec[m0 + mm];
-    auto value = [&](int64_t frame) -> float2 {  // frame of either range
-      uint32_t s = frame >= a.t0 ? uint32_t(a.slot_new) + uint32_t(frame - a.t0)
-                                 : uint32_t(a.slot_old) + uint32_t(frame - a.olo);
-      if (s >= uint32_t(a.capacity)) s -= uint32_t(a.capacity);
-      const float4 f = a.fscale[s];
-      return decode(*reinterpret_cast<const Word*>(base + int64_t(s) * slot_bytes), f.y, f.z, ref);
-    };
-    auto finite = [](float2 z) { return isfinite(z.x) && isfinite(z.y); };
-    for (int l0 = 0; l0 < a.n_lags; l0 += 64) {
-      const int l = l0 + lane;
-      const int64_t tau = l < a.n_lags ? int64_t(a.lags[l]) : a.t1;
-      float extra = 0.f;
-      bool done = false;
-      // Frames in either range, each once.
-      const int64_t end1 = a.olo + a.olen < a.t0 ? a.olo + a.olen : a.t0;
-      for (int part = 0; part < 2 && !done; ++part) {
-        const int64_t f0 = part ? a.t0 : int64_t(a.olo), f1 = part ? a.t1 : end1;
-        for (int64_t c = f0; c < f1 && !done; c += 64) {
-          const int64_t f = c + lane;
-          unsigned long long bad = __ballot(f < f1 && !finite(value(f < f1 ? f : f0)));
-          while (bad && !done) {
-            const int64_t t = c + __builtin_ctzll(bad);
-            bad &= bad - 1;
-            const float2 z = value(t);
-            // As the later frame of a pair, then as the earlier one of a
-            // pair whose later frame is finite (else it is counted there).
-            if (t >= a.t0 && t >= tau && tau < a.t1) {
-              const float2 o = value(t - tau);
-              const float dx = z.x - o.x, dy = z.y - o.y;
-              extra = fmaf(dx, dx, fmaf(dy, dy, extra));
-            }
-            if (t + tau >= a.t0 && t + tau < a.t1) {
-              const float2 n = value(t + tau);
-              if (finite(n)) {
-                const float dx = n.x - z.x, dy = n.y - z.y;
-                extra = fmaf(dx, dx, fmaf(dy, dy, extra));
-              }
-            }
-            done = __all(isnan(extra) || l >= a.n_lags);
-          }
+    if (m0 + mm >= a.n_modes) continue;
+    const auto* z = reinterpret_cast<const float2*>(smem + mm * mode_lds);
+    for (int l0 = 0; l0 < a.tab.n_paired; l0 += 64) {
+      const unsigned* bits = small + mm * (kMxLags / 32) + (l0 >> 5);
+      const unsigned long long mask = (static_cast<unsigned long long>(bits[1]) << 32) | bits[0];
+      if (!mask) continue;
+      const bool mine = mask >> lane & 1;
+      // Targets t0 + r, r >= first, and the older frames' places.
+      const int64_t tau = a.lags[l0 + (mine ? lane : __builtin_ctzll(mask))];
+      const int first = mine ? int(max(tau - a.t0, int64_t(0))) : tn;
+      const int older = int(a.t0 - tau - a.olo) + a.obase;
+      int r = int(max(int64_t(a.lags[l0 + __builtin_ctzll(mask)]) - a.t0, int64_t(0)));
+      double sum = 0.0;
+      for (; r < tn; r += 8) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float2 x = z[a.tbase + min(r + i, tn - 1)];
+          const float2 o = z[min(max(older + r + i, 0), pl - 1)];
+          const float dx = x.x - o.x, dy = x.y - o.y;
+          if (r + i >= first && r + i < tn) sum += double(fmaf(dx, dx, dy * dy));
         }
       }
-      if (l < a.n_lags && extra != 0.f)
-        atomicAdd(a.acc + (m0 + mm) * a.acc_pitch + l, extra);
+      if (mine) add_sum(m0 + mm, l0 + lane, float(sum));
     }
   }
 }
