@@ -2,8 +2,8 @@
 // time series a launch forms, and where frames lie in its LDS planes.
 // Host-only, no HIP dependency.
 //
-// The kernel holds every coefficient of a mode's time series as a 26-bit
-// integer in four signed bytes, one byte plane per digit, and forms
+// The kernel holds every coefficient of a mode's time series as a whole number
+// of 31 bits at most in four signed bytes, one byte plane per digit, and forms
 //   C_lag = sum_t q[t] q[t - lag]
 // by 16 x 16 x 64 byte matrix products: the 16 rows are the older series
 // shifted back by four 16-frame blocks times 4 digits, the 16 columns the
@@ -39,6 +39,14 @@ constexpr int kMxRounds = 5;  // of octets that a thread loads at most
 constexpr int kMxPlane = 2240;
 // LDS of one workgroup, half a CU's.
 constexpr int kMxLds = 80 * 1024;
+// Scale 2^mx_exponent of a mode whose squares over a launch's frames sum to the
+// FP32 number with bits `energy`, normal: to at most 2^61, so that a sum of squared
+// differences, at most four times that, stays below 2^64 whatever the signs, and
+// the numbers below 2^31 - 2^24.
+constexpr int mx_exponent(uint32_t energy) { return (187 - int(energy >> 23 & 255)) >> 1; }
+// Energies that this is right for: of squares that FP32 holds.
+constexpr float kMxMost = 3.4028235e38f;
+constexpr float kMxFew = 0x1p-100f;
 // Sums below this many steps^2 of a mode's whole numbers are formed again from
 // its coefficients. Rounding them moves a sum of P pairs by 0.82 / sqrt(S) of
 // itself (rms; at most 2.9 sqrt(P / S)): 2^-24 at the line, the rounding of one

@@ -1,13 +1,13 @@
 // Lag-pair sums on the matrix cores. For every stored mode and delay
 //   S_tau = sum_t |a_t - a_{t-tau}|^2
 //         = sum_t |a_t|^2 + sum_t |a_{t-tau}|^2 - 2 Re sum_t a_t conj(a_{t-tau})
-// is formed in integers: a mode's coefficients in the window are scaled by
-// one power of two to at most 2^25 in magnitude, rounded to whole numbers
-// (FP32 keeps 24 bits, so the largest are kept exactly) and all sums are
-// exact modulo 2^64, which holds S_tau itself (2 * 2^52 * pairs < 2^64). So
-// nothing cancels: equal frames give exactly 0, and the only rounding is
-// that of the coefficients, at most 2^-26 of the mode's largest. A sum that this
-// rounding reaches is summed again from the coefficients themselves: below
+// is formed in integers: a mode's coefficients in the window are scaled by one
+// power of two and rounded to whole numbers, and all sums are exact modulo 2^64.
+// The scale makes the sum of their squares, E, at most 2^61, so every S_tau, at
+// most 4 E, is held itself, and every number has 31 bits at most (mx_exponent). So
+// nothing cancels: equal frames give exactly 0, and the only rounding is that
+// of the coefficients: for 1000 of like size about 2^-26 of theirs. A sum that
+// this rounding reaches is summed again from the coefficients themselves: below
 // kMxLeast steps^2 (few pairs, slow modes, or one frame far larger than the
 // others), and all sums of a mode with a value that is not finite.
 //
@@ -242,14 +242,15 @@ __device__ __forceinline__ unsigned long long energy_in_octet(const char* planes
       }
     }
   }
-  // Every partial sum fits 32 bits: at most 16 * 2^14 per product sum, and the
-  // top digit is at most 2 in magnitude.
+  // Product sums are at most 16 * 2^14, two of them in cross[3]; of the last line
+  // the low 32 bits count.
   const int e0 = same[0] + cross[1] * (1 << 9);
   const int e16 = 2 * cross[2] + same[1] + cross[3] * (1 << 9);
-  const int e32 = 2 * cross[4] + same[2] + cross[5] * (1 << 9) + same[3] * (1 << 16);
+  const unsigned e32 = 2 * unsigned(cross[4]) + unsigned(same[2]) + (unsigned(cross[5]) << 9) +
+                       (unsigned(same[3]) << 16);
   return static_cast<unsigned long long>(static_cast<long long>(e0)) +
          (static_cast<unsigned long long>(static_cast<long long>(e16)) << 16) +
-         (static_cast<unsigned long long>(unsigned(e32)) << 32);
+         (static_cast<unsigned long long>(e32) << 32);
 }
 
 // Energy of the frame at plane place x.
@@ -278,12 +279,12 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   const int mode_lds = 9 * pl;
   const int lds0 = lds_address(smem);
   auto* tot = reinterpret_cast<unsigned long long*>(smem + km * mode_lds);  // [rounds][waves][km]
-  auto* top = reinterpret_cast<unsigned*>(tot + ROUNDS * kMxWaves * km);     // [waves][km]
-  // marks[0]: some value of the workgroup is not finite, [1]: some sum is small;
-  // small: its sums that are, a bit per mode and delay index.
-  auto* marks = top + kMxWaves * km;
-  auto* small = marks + 2;
-  for (int e = tid; e < 2 + kMxLags / 32 * km; e += THREADS) marks[e] = 0;
+  auto* squares = reinterpret_cast<float*>(tot + ROUNDS * kMxWaves * km);    // [waves][km]
+  // Whether some sum of the workgroup is small, and which: a bit per mode and
+  // delay index.
+  auto* any_small = reinterpret_cast<unsigned*>(squares + kMxWaves * km);
+  auto* small = any_small + 1;
+  for (int e = tid; e < 1 + kMxLags / 32 * km; e += THREADS) any_small[e] = 0;
 
   // Workgroups are dispatched round robin over the 8 XCDs; neighbouring
   // workgroups, whose modes share lines of the ring, stay on one XCD's L2.
@@ -424,38 +425,33 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       for (int i = 0; i < 8; ++i) v[r][i] = make_float2(0.f, 0.f);
     }
   }
-  float largest_abs = 0.f;  // NaN when a value is
+  float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r)
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      largest_abs = __builtin_elementwise_maximum(
-          largest_abs, __builtin_elementwise_maximum(fabsf(v[r][i].x), fabsf(v[r][i].y)));
-  unsigned big = __float_as_uint(largest_abs) & 0x7fffffffu;  // as bits, in order
-  for (int o = km; o < 64; o <<= 1) big = max(big, unsigned(__shfl_xor(int(big), o, 64)));
-  if (lane < km) top[wave * km + lane] = big;
-  if (big >= 0x7f800000u) marks[0] = 1;
+      part[i & 3] = fmaf(v[r][i].x, v[r][i].x, fmaf(v[r][i].y, v[r][i].y, part[i & 3]));
+  float square = (part[0] + part[1]) + (part[2] + part[3]);
+  for (int o = km; o < 64; o <<= 1) square += __shfl_xor(square, o, 64);
+  if (lane < km) squares[wave * km + lane] = square;
   __syncthreads();
 
-  // Scale 2^exponent to at most 2^25 for the mode's largest number. A mode with a
-  // value that is not finite becomes 0 here: all its sums are small.
-  auto largest = [&](int mode) -> unsigned {
-    unsigned b = 0;
-#pragma unroll
-    for (int w = 0; w < kMxWaves; ++w) b = max(b, top[w * km + mode]);
-    return b;
+  // The mode's sum of squares, which gives its scale 2^exponent. A mode whose
+  // squares pass FP32, or lie where it loses them, becomes 0 here: all its sums
+  // are small.
+  static_assert(kMxWaves == 4, "a sum of four");
+  auto squares_of = [&](int mode) -> float {
+    return (squares[mode] + squares[km + mode]) + (squares[2 * km + mode] + squares[3 * km + mode]);
   };
-  if (marks[0] && largest(lm) >= 0x7f800000u) {
+  auto exponent = [](float e) -> int { return mx_exponent(__float_as_uint(e)); };
+  const float energy = squares_of(lm);
+  if (!(energy <= kMxMost) || (energy < kMxFew && energy != 0.f)) {
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r)
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[r][i] = make_float2(0.f, 0.f);
   }
-  auto exponent = [](unsigned b) -> int {
-    const int e = int(b >> 23);
-    return 25 - ((e < 1 ? 1 : e) - 126);
-  };
-  const int ex = exponent(largest(lm));
+  const int ex = exponent(energy);
   unsigned long long sums[ROUNDS];
   char* const planes_m = smem + lm * mode_lds;
 #pragma unroll
@@ -565,7 +561,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
 
     for (int mm = wave & (km - 1); mm < km; mm += kMxWaves) {
       const char* planes = smem + mm * mode_lds;
-      const int back = -2 * exponent(largest(mm));
+      const int back = -2 * exponent(squares_of(mm));
       const bool stored = m0 + mm < a.n_modes;
 
       // Energies of a delay: targets [from, t1) and older frames [from - tau,
@@ -576,11 +572,11 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       if (a.t0 > 0) at_t0 = prefix_at(planes, pl, a.tbase);
       // S of delay index l into the running sums, or to the small ones. A mode
       // of zeros has no small sums.
-      const unsigned long long least = largest(mm) ? kMxLeast : 0;
+      const unsigned long long least = squares_of(mm) == 0.f ? 0 : kMxLeast;
       auto put = [&](int l, unsigned long long S) {
         if (S < least) {
           atomicOr(&small[mm * (kMxLags / 32) + (l >> 5)], 1u << (l & 31));
-          marks[1] = 1;
+          *any_small = 1;
           return;
         }
         add_sum(m0 + mm, l, float(ldexp(double(S), back)));
@@ -701,7 +697,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   // ---- small sums, explicitly: the coefficients take the planes' room, a wave
   // a mode's delays on its lanes, FP32 terms into an FP64 sum ----
   __syncthreads();
-  if (!marks[1]) return;
+  if (!*any_small) return;
   for (int oct = oct0; oct < octets; oct += step)
     for (int i = 0; i < 8; ++i) {
       const int slot = slot_at(8 * oct + i);
