@@ -86,7 +86,7 @@ enum { NFS_IN_U16 = 0, NFS_IN_F32 = 1 };
  * Differences, squares and sums are FP32 in every case (precision form), or,
  * for windows with many delays, exact sums of whole numbers: a mode's values
  * in the window scaled by one power of two, which brings the sum of their squares
- * to 2^59 .. 2^61, and rounded (their differences then carry no further rounding).
+ * to 2^60 .. 2^62, and rounded (their differences then carry no further rounding).
  * Sums that this rounding could move by more than FP32 terms' own are FP32 there
  * too. */
 enum { NFS_SPEC_F32 = 0, NFS_SPEC_BF16 = 1, NFS_SPEC_F16 = 2 };

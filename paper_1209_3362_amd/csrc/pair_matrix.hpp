@@ -39,11 +39,12 @@ constexpr int kMxRounds = 5;  // of octets that a thread loads at most
 constexpr int kMxPlane = 2240;
 // LDS of one workgroup, half a CU's.
 constexpr int kMxLds = 80 * 1024;
-// Scale 2^mx_exponent of a mode whose squares over a launch's frames sum to the
-// FP32 number with bits `energy`, normal: to at most 2^61, so that a sum of squared
-// differences, at most four times that, stays below 2^64 whatever the signs, and
-// the numbers below 2^31 - 2^24.
-constexpr int mx_exponent(uint32_t energy) { return (187 - int(energy >> 23 & 255)) >> 1; }
+// Scale 2^mx_exponent of a mode whose squares over a launch's frames sum to E, with
+// the bits of the normal FP32 number kMxRoom * E: it takes E to 0.94 * 2^60 .. 0.94 * 2^62,
+// so that a sum of squared differences, at most four times that, stays below 2^64
+// whatever the signs, and the numbers below 2^31 - 2^24.
+constexpr float kMxRoom = 1.0625f;
+constexpr int mx_exponent(uint32_t bits) { return (188 - int(bits >> 23 & 255)) >> 1; }
 // Energies that this is right for: of squares that FP32 holds.
 constexpr float kMxMost = 3.4028235e38f;
 constexpr float kMxFew = 0x1p-100f;

@@ -3,7 +3,7 @@
 //         = sum_t |a_t|^2 + sum_t |a_{t-tau}|^2 - 2 Re sum_t a_t conj(a_{t-tau})
 // is formed in integers: a mode's coefficients in the window are scaled by one
 // power of two and rounded to whole numbers, and all sums are exact modulo 2^64.
-// The scale makes the sum of their squares, E, at most 2^61, so every S_tau, at
+// The scale makes the sum of their squares, E, less than 2^62, so every S_tau, at
 // most 4 E, is held itself, and every number has 31 bits at most (mx_exponent). So
 // nothing cancels: equal frames give exactly 0, and the only rounding is that
 // of the coefficients: for 1000 of like size about 2^-26 of theirs. A sum that
@@ -270,6 +270,127 @@ __device__ __forceinline__ unsigned long long prefix_at(const char* planes, int 
   return *reinterpret_cast<const unsigned long long*>(planes + 8 * pl + (x & ~7));
 }
 
+// Ring slot of plane place x, or -1 where no frame lies.
+__device__ __forceinline__ int slot_at(const MxArgs& a, int x) {
+  const bool old = x < a.split;
+  const int f = x - (old ? a.obase : a.tbase);
+  const int n = old ? a.olen : int(a.t1 - a.t0);
+  uint32_t s = uint32_t(old ? a.slot_old : a.slot_new) + uint32_t(f);
+  if (s >= uint32_t(a.capacity)) s -= uint32_t(a.capacity);
+  return f >= 0 && f < n ? int(s) : -1;
+}
+
+// Stored words of a mode, and their value: decoded, scaled by 2^-e (16-bit
+// storage) and corrected by d times the reference transform.
+template <int SPEC>
+using MxWord = std::conditional_t<SPEC == kSpecF32, float2, uint32_t>;
+template <int SPEC>
+__device__ __forceinline__ float2 decode(MxWord<SPEC> w, float d, float inv, float2 ref) {
+  float2 v;
+  if constexpr (SPEC == kSpecF32) {
+    v = w;
+  } else {
+    v = SPEC == kSpecBF16 ? dev::unpack_bf16(w) : dev::unpack_f16(w);
+    v.x *= inv;
+    v.y *= inv;
+  }
+  return make_float2(fmaf(d, ref.x, v.x), fmaf(d, ref.y, v.y));
+}
+
+// A launch's sum of delay index l into the running sum.
+__device__ __forceinline__ void add_sum(const MxArgs& a, int64_t mode, int l, float val) {
+  float* sum = a.acc + mode * a.acc_pitch + l;
+  if (a.comp) {
+    // With Kahan compensation.
+    float* comp = a.comp + mode * a.acc_pitch + l;
+    if (a.assign) {
+      *sum = val;
+      *comp = 0.f;
+    } else {
+      const float was = *sum;
+      const float y = val - *comp;
+      const float t = was + y;
+      *comp = (t - was) - y;
+      *sum = t;
+    }
+  } else {
+    *sum = a.assign ? val : *sum + val;
+  }
+}
+
+// LDS after the planes, the rounds' totals and the sums of squares: the first delay
+// with a small sum in the workgroup, then the small sums, a bit per mode and
+// delay index.
+__device__ __forceinline__ int* first_small_of(int km, int pl) {
+  return reinterpret_cast<int*>(smem + km * (9 * pl + kMxRounds * kMxWaves * 8 + kMxWaves * 4));
+}
+
+// The kernel's arguments, read again: kept from its beginning on they would take
+// the registers of its loops.
+__device__ __forceinline__ const MxArgs& kernel_args() {
+  auto* p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const MxArgs*)(p);
+}
+
+// The workgroup's small sums from the coefficients themselves, which take the
+// planes' room: a wave a mode's delays on its lanes, FP32 terms into an FP64 sum.
+template <int SPEC>
+__device__ __forceinline__ void sum_small(const MxArgs& a, int64_t m0) {
+  constexpr int THREADS = 64 * kMxWaves;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int km = 1 << a.km_log2, pl = a.pl, mode_lds = 9 * pl;
+  const int tn = int(a.t1 - a.t0);
+  const int* first_small = first_small_of(km, pl);
+  const auto* small = reinterpret_cast<const unsigned*>(first_small + 1);
+  // Their targets begin at place x0, their older frames end at x1.
+  const int64_t least_lag = a.lags[*first_small];
+  const int x0 = a.tbase + int(max(least_lag - a.t0, int64_t(0)));
+  const int x1 = a.obase + int(a.t1 - least_lag - a.olo);
+  const int lm = tid & (km - 1);
+  const float2 ref = a.refspec[m0 + lm];
+  const auto* ring = reinterpret_cast<const MxWord<SPEC>*>(a.ring) + m0 + lm;
+  auto* values = reinterpret_cast<float2*>(smem + lm * mode_lds);
+  for (int oct = tid >> a.km_log2; oct < pl >> 3; oct += THREADS >> a.km_log2) {
+    if (8 * oct + 8 <= x0 && 8 * oct >= x1) continue;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int slot = slot_at(a, 8 * oct + i);
+      const float4 f = a.fscale[max(slot, 0)];
+      const float2 v = decode<SPEC>(ring[max(slot, 0) * a.mode_stride], f.y, f.z, ref);
+      values[8 * oct + i] = slot >= 0 ? v : make_float2(0.f, 0.f);
+    }
+  }
+  __syncthreads();
+  for (int mm = wave; mm < km; mm += kMxWaves) {
+    if (m0 + mm >= a.n_modes) continue;
+    const auto* z = reinterpret_cast<const float2*>(smem + mm * mode_lds);
+    for (int l0 = 0; l0 < a.tab.n_paired; l0 += 64) {
+      const unsigned* bits = small + mm * (kMxLags / 32) + (l0 >> 5);
+      const unsigned long long mask = (static_cast<unsigned long long>(bits[1]) << 32) | bits[0];
+      if (!mask) continue;
+      const bool mine = mask >> lane & 1;
+      const int64_t lag0 = a.lags[l0 + __builtin_ctzll(mask)];
+      const int64_t tau = mine ? int64_t(a.lags[l0 + lane]) : lag0;
+      // Targets t0 + r, r >= first, and the older frames' places.
+      const int first = mine ? int(max(tau - a.t0, int64_t(0))) : tn;
+      const int older = int(a.t0 - tau - a.olo) + a.obase;
+      double sum = 0.0;
+      for (int r = int(max(lag0 - a.t0, int64_t(0))); r < tn; r += 8) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float2 x = z[a.tbase + min(r + i, tn - 1)];
+          const float2 o = z[min(max(older + r + i, 0), pl - 1)];
+          const float dx = x.x - o.x, dy = x.y - o.y;
+          if (r + i >= first && r + i < tn) sum += double(fmaf(dx, dx, dy * dy));
+        }
+      }
+      if (mine) add_sum(a, m0 + mm, l0 + lane, float(sum));
+    }
+  }
+}
+
 template <int SPEC>
 __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs a) {
   constexpr int THREADS = 64 * kMxWaves, ROUNDS = kMxRounds;
@@ -280,11 +401,10 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   const int lds0 = lds_address(smem);
   auto* tot = reinterpret_cast<unsigned long long*>(smem + km * mode_lds);  // [rounds][waves][km]
   auto* squares = reinterpret_cast<float*>(tot + ROUNDS * kMxWaves * km);    // [waves][km]
-  // Whether some sum of the workgroup is small, and which: a bit per mode and
-  // delay index.
-  auto* any_small = reinterpret_cast<unsigned*>(squares + kMxWaves * km);
-  auto* small = any_small + 1;
-  for (int e = tid; e < 1 + kMxLags / 32 * km; e += THREADS) any_small[e] = 0;
+  int* first_small = first_small_of(km, pl);
+  auto* small = reinterpret_cast<unsigned*>(first_small + 1);
+  if (tid == 0) *first_small = kMxLags;
+  for (int e = tid; e < kMxLags / 32 * km; e += THREADS) small[e] = 0;
 
   // Workgroups are dispatched round robin over the 8 XCDs; neighbouring
   // workgroups, whose modes share lines of the ring, stay on one XCD's L2.
@@ -324,35 +444,13 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   constexpr int MODE_BYTES = SPEC == kSpecF32 ? 8 : 4;
   const char* ring_m = a.ring + m * MODE_BYTES;
   const int64_t slot_bytes = a.mode_stride * MODE_BYTES;
-  // Ring slot of plane place x, or -1 where no frame lies.
-  auto slot_at = [&](int x) -> int {
-    const bool old = x < a.split;
-    const int f = x - (old ? a.obase : a.tbase);
-    const int n = old ? a.olen : int(a.t1 - a.t0);
-    uint32_t s = uint32_t(old ? a.slot_old : a.slot_new) + uint32_t(f);
-    if (s >= uint32_t(a.capacity)) s -= uint32_t(a.capacity);
-    return f >= 0 && f < n ? int(s) : -1;
-  };
-  // Stored words of a mode, and their value: decoded, scaled by 2^-e (16-bit
-  // storage) and corrected by d times the reference transform.
-  using Word = std::conditional_t<SPEC == kSpecF32, float2, uint32_t>;
-  auto decode = [](Word w, float d, float inv, float2 ref) -> float2 {
-    float2 v;
-    if constexpr (SPEC == kSpecF32) {
-      v = w;
-    } else {
-      v = SPEC == kSpecBF16 ? dev::unpack_bf16(w) : dev::unpack_f16(w);
-      v.x *= inv;
-      v.y *= inv;
-    }
-    return make_float2(fmaf(d, ref.x, v.x), fmaf(d, ref.y, v.y));
-  };
+  using Word = MxWord<SPEC>;
   // The frames' {d, 2^-e} by plane place ({0, 0} where none lies), in the room
   // that the planes take later.
   float* tab_d = reinterpret_cast<float*>(smem);
   float* tab_s = tab_d + pl;
   for (int x = tid; x < pl; x += THREADS) {
-    const int slot = slot_at(x);
+    const int slot = slot_at(a, x);
     const float4 f = a.fscale[max(slot, 0)];
     tab_d[x] = slot >= 0 ? f.y : 0.f;
     if constexpr (SPEC != kSpecF32) tab_s[x] = slot >= 0 ? f.z : 0.f;
@@ -399,7 +497,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       if (oct < octets) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const int slot = slot_at(8 * oct + i);
+          const int slot = slot_at(a, 8 * oct + i);
           const Word w = *reinterpret_cast<const Word*>(ring_m + max(slot, 0) * slot_bytes);
           raw[r][i] = slot >= 0 ? w : Word{};
         }
@@ -419,7 +517,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
         inv[i] = SPEC == kSpecF32 ? 0.f : tab_s[8 * oct + i];
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[r][i] = decode(raw[r][i], d[i], inv[i], R);
+      for (int i = 0; i < 8; ++i) v[r][i] = decode<SPEC>(raw[r][i], d[i], inv[i], R);
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[r][i] = make_float2(0.f, 0.f);
@@ -443,7 +541,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   auto squares_of = [&](int mode) -> float {
     return (squares[mode] + squares[km + mode]) + (squares[2 * km + mode] + squares[3 * km + mode]);
   };
-  auto exponent = [](float e) -> int { return mx_exponent(__float_as_uint(e)); };
+  auto exponent = [](float e) -> int { return mx_exponent(__float_as_uint(kMxRoom * e)); };
   const float energy = squares_of(lm);
   if (!(energy <= kMxMost) || (energy < kMxFew && energy != 0.f)) {
 #pragma unroll
@@ -520,26 +618,6 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
   }
   __syncthreads();
 
-  // A window's sum of delay index l into the running sum.
-  auto add_sum = [&](int64_t mode, int l, float val) {
-    float* sum = a.acc + mode * a.acc_pitch + l;
-    if (a.comp) {
-      float* comp = a.comp + mode * a.acc_pitch + l;
-      if (a.assign) {
-        *sum = val;
-        *comp = 0.f;
-      } else {
-        const float was = *sum;
-        const float y = val - *comp;
-        const float t = was + y;
-        *comp = (t - was) - y;
-        *sum = t;
-      }
-    } else {
-      *sum = a.assign ? val : *sum + val;
-    }
-  };
-
   // ---- products: waves take modes, and tasks when there are more waves ----
   const int tn = int(a.t1 - a.t0);
   const int share = km < kMxWaves ? kMxWaves / km : 1;
@@ -572,14 +650,15 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
       if (a.t0 > 0) at_t0 = prefix_at(planes, pl, a.tbase);
       // S of delay index l into the running sums, or to the small ones. A mode
       // of zeros has no small sums.
-      const unsigned long long least = squares_of(mm) == 0.f ? 0 : kMxLeast;
+      static_assert(kMxLeast << 32 == 0, "the high word decides");
+      const unsigned least = squares_of(mm) == 0.f ? 0 : unsigned(kMxLeast >> 32);
       auto put = [&](int l, unsigned long long S) {
-        if (S < least) {
+        if (unsigned(S >> 32) < least) {
           atomicOr(&small[mm * (kMxLags / 32) + (l >> 5)], 1u << (l & 31));
-          *any_small = 1;
+          atomicMin(first_small, l);
           return;
         }
-        add_sum(m0 + mm, l, float(ldexp(double(S), back)));
+        add_sum(a, m0 + mm, l, float(ldexp(double(S), back)));
       };
       // Four tiles' sums (lane: delay place lane / 4, target digit lane % 4) to
       // cross sums modulo 2^64: class lane % 4 of place lane / 4.
@@ -694,45 +773,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 2) void pair_mx_kernel(const MxArgs 
     }
   }
 
-  // ---- small sums, explicitly: the coefficients take the planes' room, a wave
-  // a mode's delays on its lanes, FP32 terms into an FP64 sum ----
   __syncthreads();
-  if (!*any_small) return;
-  for (int oct = oct0; oct < octets; oct += step)
-    for (int i = 0; i < 8; ++i) {
-      const int slot = slot_at(8 * oct + i);
-      const float4 f = a.fscale[max(slot, 0)];
-      const Word w = *reinterpret_cast<const Word*>(ring_m + max(slot, 0) * slot_bytes);
-      reinterpret_cast<float2*>(planes_m)[8 * oct + i] =
-          slot >= 0 ? decode(w, f.y, f.z, R) : make_float2(0.f, 0.f);
-    }
-  __syncthreads();
-  for (int mm = wave; mm < km; mm += kMxWaves) {
-    if (m0 + mm >= a.n_modes) continue;
-    const auto* z = reinterpret_cast<const float2*>(smem + mm * mode_lds);
-    for (int l0 = 0; l0 < a.tab.n_paired; l0 += 64) {
-      const unsigned* bits = small + mm * (kMxLags / 32) + (l0 >> 5);
-      const unsigned long long mask = (static_cast<unsigned long long>(bits[1]) << 32) | bits[0];
-      if (!mask) continue;
-      const bool mine = mask >> lane & 1;
-      // Targets t0 + r, r >= first, and the older frames' places.
-      const int64_t tau = a.lags[l0 + (mine ? lane : __builtin_ctzll(mask))];
-      const int first = mine ? int(max(tau - a.t0, int64_t(0))) : tn;
-      const int older = int(a.t0 - tau - a.olo) + a.obase;
-      int r = int(max(int64_t(a.lags[l0 + __builtin_ctzll(mask)]) - a.t0, int64_t(0)));
-      double sum = 0.0;
-      for (; r < tn; r += 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float2 x = z[a.tbase + min(r + i, tn - 1)];
-          const float2 o = z[min(max(older + r + i, 0), pl - 1)];
-          const float dx = x.x - o.x, dy = x.y - o.y;
-          if (r + i >= first && r + i < tn) sum += double(fmaf(dx, dx, dy * dy));
-        }
-      }
-      if (mine) add_sum(m0 + mm, l0 + lane, float(sum));
-    }
-  }
+  if (*first_small != kMxLags) sum_small<SPEC>(kernel_args(), m0);
 }
 
 }  // namespace

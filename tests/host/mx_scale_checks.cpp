@@ -44,7 +44,8 @@ void check_series(const char* what, const std::vector<float>& x, const std::vect
   for (size_t t = 0; t < x.size(); ++t) energy = std::fma(x[t], x[t], std::fma(y[t], y[t], energy));
   if (!(energy <= kMxMost) || energy < kMxFew) return;
   uint32_t bits;
-  std::memcpy(&bits, &energy, 4);
+  const float roomy = kMxRoom * energy;
+  std::memcpy(&bits, &roomy, 4);
   const int ex = mx_exponent(bits);
   std::vector<int64_t> q[2];
   double squares = 0.0;
@@ -59,7 +60,7 @@ void check_series(const char* what, const std::vector<float>& x, const std::vect
       q[comp].push_back(v);
       squares += double(v) * double(v);
     }
-  CHECK(squares > 0x1p58 && squares < 0x1.01p61, "%s: squares %g", what, squares);
+  CHECK(squares > 0x1.dp59 && squares < 0x1.fp61, "%s: squares %g", what, squares);
   for (size_t tau : {size_t(1), size_t(2), size_t(3), x.size() / 2, x.size() - 1}) {
     uint64_t S = 0;
     long double exact = 0;
