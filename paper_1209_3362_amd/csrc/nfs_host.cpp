@@ -224,8 +224,8 @@ nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
   o.fused_slots = (o.batch + 7) / 8;  // frames per XCD per launch at most
   o.off_sched = take(o.fused_ok ? size_t(8 * 64 + 16 * o.fused_slots) * 4 : 0);
   const size_t nseg = o.seg_first.size() - 1;
-  // Tables in three runs of neighbours, each one upload: segs and bin_slots, tw to
-  // lags, mode_bin and bin_count.
+  // Tables in three runs of neighbours, each one upload: segs and bin_slots, status
+  // (zeros) to lags, mode_bin and bin_count.
   o.off_segs = take((o.seg_first.size() + o.bin_seg0.size()) * 4);
   o.off_bin_slots = take(ring_modes * 4);
   o.off_part = take(nseg * o.n_lags * 8);
