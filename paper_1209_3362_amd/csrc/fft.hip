@@ -337,7 +337,7 @@ __device__ __forceinline__ void write_reference_scale(double total, double sigma
 // fscale[slot].z (1 otherwise). Per-thread store offsets are computed once;
 // the next frame's columns are loaded during the second level.
 template <int N, bool REF, int SPEC>
-__global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_kernel(
+__global__ __launch_bounds__(ColCfg<N>::THREADS, 2) void col_pass_kernel(
     const float2* __restrict__ inter, const double* __restrict__ rowsum,
     const double* __restrict__ rowabs, double* __restrict__ refscal,
     float4* __restrict__ fscale, int32_t* __restrict__ status, int nframes, int per_group,
@@ -378,23 +378,17 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
   // Outputs of this thread: rows r = (j1 + q P1) + P2 k1 of column kx,
   // stored at byte offset 8 ring_slot(r, kx) of the spectrum (tiled slot
   // layout: a workgroup's columns fill one contiguous block), or not at all
-  // (kDropOffset) when the row is not kept in the column's tile. Up to 32
-  // outputs per thread the offsets stay in registers across frames; more
-  // are looked up again per frame.
-  constexpr bool CACHE = Q * P1 <= 32;
-  constexpr int QC = CACHE ? Q : 1, PC = CACHE ? P1 : 1;
-  auto store_offset = [&](int q, int k1) -> uint32_t {
-    const int r = (j1 + q * P1) + P2 * k1;
-    const int slot = ring_slot(N, tiles, r, kx);
-    return slot >= 0 ? uint32_t(slot) * 8u : kDropOffset;
-  };
-  uint32_t at[QC][PC];
-  if constexpr (CACHE) {
+  // (kDropOffset) when the row is not kept in the column's tile. The offsets
+  // stay in registers across frames.
+  static_assert(N < 2048 && Q * P1 <= 32, "longer columns take col3_pass_kernel");
+  uint32_t at[Q][P1];
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
-      for (int k1 = 0; k1 < P1; ++k1) at[q][k1] = store_offset(q, k1);
-  }
+    for (int k1 = 0; k1 < P1; ++k1) {
+      const int slot = ring_slot(N, tiles, (j1 + q * P1) + P2 * k1, kx);
+      at[q][k1] = slot >= 0 ? uint32_t(slot) * 8u : kDropOffset;
+    }
 
   auto load_cols = [&](float2 (&v)[P2], int f) {
     // Column kx is column kx % TWD of tile kx / TWD of the intermediate.
@@ -403,7 +397,7 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
     for (int j2 = 0; j2 < P2; ++j2) v[j2] = src[(j1 + P1 * j2) * TWD];
   };
   float2 v[P2];
-  if (CACHE && f_begin < f_end) load_cols(v, f_begin);
+  if (f_begin < f_end) load_cols(v, f_begin);
   float2* col_lds = lds + c * CP;
   int64_t slot = (t0 + f_begin) % capacity;
   double s_ref = 0.0, sigma_ref = 0.0;
@@ -431,7 +425,6 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
     if constexpr (F16) {
       for (int y = tid; y < N; y += THREADS) part_abs += rowabs[int64_t(f) * N + y];
     }
-    if constexpr (!CACHE) load_cols(v, f);
     dft<P2>(v);
     static_for<P2>([&](auto K2) {
       constexpr int k2 = decltype(K2)::value;
@@ -450,9 +443,7 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
       if ((tid & 63) == 0) red_abs[tid >> 6] = part_abs;
     }
     __syncthreads();
-    if constexpr (CACHE) {
-      if (f + 1 < f_end) load_cols(v, f + 1);
-    }
+    if (f + 1 < f_end) load_cols(v, f + 1);
 
     float scale = 1.f;
     const bool reference = FIRST && f == nframes;
@@ -497,8 +488,7 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS, ColCfg<N>::MINW) void col_pass_
         dft<P1>(w);
         static_for<P1>([&](auto K1) {
           constexpr int k1 = decltype(K1)::value;
-          uint32_t o;
-          if constexpr (CACHE) o = at[q][k1]; else o = store_offset(q, k1);
+          const uint32_t o = at[q][k1];
           float2 X = w[bitrev<P1>(k1)];
           if constexpr (!REF) {
             X.x *= scale;

@@ -32,9 +32,10 @@ struct ColCfg {
   static constexpr int P2 = N / P1;
   static constexpr int Q = P2 / P1;
   static constexpr int CP = pad_2mod16(P2 * (P1 + 1));
-  // Up to n = 1024 the exchange twiddles sit in LDS; from 2048 on a column
-  // alone takes 16 KB of LDS, so the table is read through the L1 cache
-  // instead and the freed LDS holds twice the columns per workgroup.
+  // Up to n = 1024 the exchange twiddles sit in LDS; from 2048 on (the inverse
+  // transforms only: the column pass has Col3Cfg there) a column alone takes
+  // 16 KB of LDS, so the table is read through the L1 cache instead and the
+  // freed LDS holds twice the columns per workgroup.
   static constexpr bool TW_LDS = N < 2048;
   static constexpr int TWL = TW_LDS ? tw_len(N) : 1;     // LDS twiddle entries
   static constexpr int CW = fit_cols(CP, TW_LDS ? tw_len(N) * 8 : 0);  // columns per workgroup
@@ -44,9 +45,6 @@ struct ColCfg {
   // groups of this pass, or two one-column groups).
   static constexpr int TWD = CW > 2 ? CW : 2;
   static constexpr int TILES = (N / 2) / TWD;
-  // Two workgroups per CU while the per-thread store offsets fit the
-  // register budget of two waves per SIMD.
-  static constexpr int MINW = Q * P1 <= 32 ? 2 : 1;
 };
 
 // Column transforms from n = 2048 on, in three levels: n = 16 * 16 * C, every
