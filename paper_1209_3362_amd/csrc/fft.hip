@@ -90,16 +90,17 @@ __device__ __forceinline__ typename RawPair<T>::type load_pair(const T* p) {
 // of |what is transformed| (bounds every coefficient of the frame).
 // first (0 or 1; n <= kFirstMax): the batch starts a sequence and its frame 0 is
 // the reference (ref == frames). Frame 0 as it is, nothing subtracted, is then
-// transformed as one more frame `nframes` and copied to ref_out. As launches of
-// their own the reference's passes, copy and scale, with the reset's clearing,
-// took 10 of 48 us for 64 frames of 128 x 128. One instance of the kernel does
-// both kinds of batch, so that a frame's bits do not depend on how it was pushed.
+// transformed as one more frame `nframes` and copied to ref_out, and the
+// sequence's counters at `clear` are set to 0. As launches of their own the
+// reference's passes, copy and scale and the clearing took 10 of 48 us for
+// 64 frames of 128 x 128. One instance of the kernel does both kinds of batch,
+// so that a frame's bits do not depend on how it was pushed.
 template <int N, typename T, bool WIN, bool ABS>
 __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>())) void row_pass_kernel(
     const T* __restrict__ frames, const T* __restrict__ ref, const float* __restrict__ window,
     int nframes, int per_group, float2* __restrict__ inter, double* __restrict__ rowsum,
     double* __restrict__ rowabs, float* __restrict__ nyq, const float2* __restrict__ tw,
-    int first, T* __restrict__ ref_out) {
+    int first, T* __restrict__ ref_out, uint32_t* __restrict__ clear) {
   constexpr bool FIRST = N <= kFirstMax;
   using C = RowCfg<N>;
   using Raw = typename RawPair<T>::type;
@@ -116,6 +117,8 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS, (row_min_waves<N, T, WIN, ABS>(
   const int f_end = min(FIRST ? nframes + first : nframes, f_begin + per_group);
   const int y = rblk * R + rl;
   float2* row_lds = lds + rl * PITCH;
+  if (FIRST && clear && blockIdx.x == 0)
+    for (int i = tid; i < kClearWords; i += THREADS) clear[i] = 0u;
 
   for (int i = tid; i < N; i += THREADS) twl[tw_skew(i)] = tw[i];
 
@@ -1072,7 +1075,7 @@ __global__ __launch_bounds__(256, 2) void fused_transform_kernel(
 template <int N, typename T, bool WIN>
 hipError_t row_launch(const void* frames, const void* ref, const float* window, int nframes,
                       float2* inter, double* rowsum, double* rowabs, float* nyq,
-                      const float2* tw, void* ref_out, hipStream_t s) {
+                      const float2* tw, void* ref_out, uint32_t* clear, hipStream_t s) {
   using C = RowCfg<N>;
   const int first = ref_out ? 1 : 0;
   if (first && N > kFirstMax) return hipErrorInvalidValue;
@@ -1082,7 +1085,7 @@ hipError_t row_launch(const void* frames, const void* ref, const float* window, 
     hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(C::THREADS), 0, s,
                        static_cast<const T*>(frames), static_cast<const T*>(ref), window,
                        nframes, per, inter, rowsum, rowabs, nyq, tw, first,
-                       static_cast<T*>(ref_out));
+                       static_cast<T*>(ref_out), clear);
   };
   if (rowabs)
     go(row_pass_kernel<N, T, WIN, true>);
@@ -1094,9 +1097,10 @@ hipError_t row_launch(const void* frames, const void* ref, const float* window, 
 template <int N>
 hipError_t row_dispatch(int in_dtype, const void* frames, const void* ref, const float* window,
                         int nframes, float2* inter, double* rowsum, double* rowabs, float* nyq,
-                        const float2* tw, void* ref_out, hipStream_t s) {
+                        const float2* tw, void* ref_out, uint32_t* clear, hipStream_t s) {
   auto go = [&](auto launch) {
-    return launch(frames, ref, window, nframes, inter, rowsum, rowabs, nyq, tw, ref_out, s);
+    return launch(frames, ref, window, nframes, inter, rowsum, rowabs, nyq, tw, ref_out, clear,
+                  s);
   };
   if (in_dtype == 0)
     return window ? go(row_launch<N, uint16_t, true>) : go(row_launch<N, uint16_t, false>);
@@ -1151,11 +1155,11 @@ hipError_t col_launch(ColFrames which, int spec, const float2* inter, const doub
 hipError_t launch_row_pass(int n, int in_dtype, const void* frames, const void* ref,
                            const float* window, int nframes, float2* inter, double* rowsum,
                            double* rowabs, float* nyq, const float2* tw, void* ref_out,
-                           hipStream_t s) {
+                           uint32_t* clear, hipStream_t s) {
 #define NFS_ROW_CASE(NN)                                                                    \
   case NN:                                                                                  \
     return row_dispatch<NN>(in_dtype, frames, ref, window, nframes, inter, rowsum, rowabs, \
-                            nyq, tw, ref_out, s);
+                            nyq, tw, ref_out, clear, s);
   switch (n) {
     NFS_ROW_CASE(16)
     NFS_ROW_CASE(32)

@@ -60,6 +60,7 @@ struct nfs_plan_s {
   // No pair launch since the sums were reset: the next one stores its sums
   // instead of adding them, so a reset needs no fill of the sums.
   bool sums_fresh = true;
+  bool clear_due = false;  // the status block is to be cleared before its next use
   // Host pushes (host_staging): two device staging buffers of one batch;
   // copies run on `copy`, transforms on `stream`. copied[j] marks batch
   // data in buffer j, freed[j] the end of the transform that read it.
@@ -201,10 +202,13 @@ nfs_status flush_pairs(nfs_plan_s* h) {
   return NFS_OK;
 }
 
+nfs_status settle_clear(nfs_plan_s* h);
+
 // Sums ready for reading: pending pairs summed, and zeros where no pair
 // launch has run since the reset (no frames pushed).
 nfs_status finish_sums(nfs_plan_s* h) {
-  nfs_status st = flush_pairs(h);
+  nfs_status st = settle_clear(h);
+  if (st == NFS_OK) st = flush_pairs(h);
   if (st != NFS_OK || !h->sums_fresh) return st;
   const nfs::Layout& L = h->L;
   hipError_t e = nfs::launch_fill_u32(h->acc, size_t(L.n_lags) * L.mode_stride, 0u, h->stream);
@@ -216,14 +220,28 @@ nfs_status finish_sums(nfs_plan_s* h) {
 }
 
 // The status word, the reference scalars (rewritten by the next push) and the
-// work counters are the first words of the status block. They are cleared by a
-// kernel of their own at the reset: left to the first batch's launches (no
-// measured gain: 37.2 against 37.8 us for 64 frames of 128 x 128) a reset before a
-// capture would go into the graph and clear on each of its replays.
-constexpr size_t kClearWords = 20;
-nfs_status clear_sums(nfs_plan_s* h) {
-  hipError_t e = nfs::launch_fill_u32(h->status, kClearWords, 0u, h->stream);
+// work counters, the first words of the status block.
+nfs_status clear_status(nfs_plan_s* h) {
+  hipError_t e = nfs::launch_fill_u32(h->status, nfs::kClearWords, 0u, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "fill kernel launch");
+  h->clear_due = false;
+  return NFS_OK;
+}
+
+nfs_status settle_clear(nfs_plan_s* h) { return h->clear_due ? clear_status(h) : NFS_OK; }
+
+// On the legacy default stream the clearing is left to the next sequence's first
+// row pass where that takes the reference along, else to a kernel of its own
+// before the next use (32 frames of 32 x 32: 45.3 against 49.2 us a pass). Other
+// streams may be captured: a clearing put off would go into the graph of a later
+// push and clear on each of its replays.
+nfs_status clear_sums(nfs_plan_s* h) {
+  if (h->stream) {
+    nfs_status st = clear_status(h);
+    if (st != NFS_OK) return st;
+  } else {
+    h->clear_due = true;
+  }
   h->sums_fresh = true;
   h->t_pushed = 0;
   h->t_done = 0;
@@ -356,7 +374,7 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
   }
   hipError_t e = nfs::launch_row_pass(L.n, L.in_dtype, src, h->ref, h->window, int(b),
                                       w.inter, w.rowsum, w.rowabs, w.nyq, h->tw, nullptr,
-                                      h->stream);
+                                      nullptr, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "row pass launch");
   e = nfs::launch_col_pass(L.n, nfs::ColFrames::kFrames, L.spec_dtype, w.inter, w.rowsum,
                            w.rowabs, int(b), t, L.capacity, L.mode_stride, L.slots, h->tiles,
@@ -375,10 +393,12 @@ nfs_status transform_into_ring(nfs_plan_s* h, const char* src, int64_t b, int64_
 // The reference of frames above kFirstMax, by itself.
 nfs_status reference_batch(nfs_plan_s* h, const char* src) {
   const nfs::Layout& L = h->L;
+  nfs_status st = settle_clear(h);
+  if (st != NFS_OK) return st;
   hipError_t e = hipMemcpyAsync(h->ref, src, L.frame_bytes, hipMemcpyDeviceToDevice, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "reference copy");
   e = nfs::launch_row_pass(L.n, L.in_dtype, h->ref, nullptr, h->window, 1, h->inter, h->rowsum,
-                           nullptr, h->nyq, h->tw, nullptr, h->stream);
+                           nullptr, h->nyq, h->tw, nullptr, nullptr, h->stream);
   if (e == hipSuccess)
     e = nfs::launch_col_pass(L.n, nfs::ColFrames::kReference, NFS_SPEC_F32, h->inter, h->rowsum,
                              nullptr, 1, 0, L.capacity, L.mode_stride, L.slots, h->tiles, h->tw,
@@ -396,9 +416,11 @@ nfs_status reference_batch(nfs_plan_s* h, const char* src) {
 // launches of one batch. Scratch of b + 1 frames.
 nfs_status first_batch(nfs_plan_s* h, const char* src, int64_t b, const BatchScratch& w) {
   const nfs::Layout& L = h->L;
+  uint32_t* clear = h->clear_due ? reinterpret_cast<uint32_t*>(h->status) : nullptr;
   hipError_t e = nfs::launch_row_pass(L.n, L.in_dtype, src, src, h->window, int(b), w.inter,
-                                      w.rowsum, w.rowabs, w.nyq, h->tw, h->ref, h->stream);
+                                      w.rowsum, w.rowabs, w.nyq, h->tw, h->ref, clear, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "row pass launch");
+  h->clear_due = false;
   e = nfs::launch_col_pass(L.n, nfs::ColFrames::kFirst, L.spec_dtype, w.inter, w.rowsum,
                            w.rowabs, int(b), 0, L.capacity, L.mode_stride, L.slots, h->tiles,
                            h->tw, h->ring, h->refspec, h->refscal, h->fscale, h->status, h->work,
@@ -568,7 +590,7 @@ nfs_status nfs_plan(const nfs_desc* desc, void* workspace, size_t bytes, void* s
   put(L.off_segs + L.seg_first.size() * 4, L.bin_seg0);
   put(L.off_bin_slots, L.bin_slots);
   send(L.off_status);
-  put(L.off_status, std::vector<uint32_t>(kClearWords));  // as a reset leaves it
+  put(L.off_status, std::vector<uint32_t>(nfs::kClearWords));  // as a reset leaves it
   put(L.off_tw, nfs::twiddle_table(L.n));
   put(L.off_width, L.row_width);
   put(L.off_tiles, L.tiles);
@@ -881,6 +903,8 @@ nfs_status nfs_structure_function_noalloc(const nfs_desc* desc, const void* fram
 nfs_status nfs_work_counters(nfs_handle h, int64_t* counters) {
   if (!is_live(h)) return NFS_E_STATE;
   if (!counters) return fail(h, NFS_E_ARG, "counters is NULL");
+  nfs_status st = settle_clear(h);
+  if (st != NFS_OK) return st;
   hipError_t e = hipMemcpyAsync(counters, h->work, 2 * sizeof(int64_t),
                                 hipMemcpyDeviceToDevice, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "work counter copy");

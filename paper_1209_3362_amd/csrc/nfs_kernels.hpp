@@ -23,12 +23,14 @@ namespace nfs {
 // nyq: [nframes][n] floats receiving X_y(n/2) (full half-plane plans), or null.
 // ref_out (n <= kFirstMax, ref == frames): the batch starts a sequence; its frame
 // 0, nothing subtracted, is transformed as one more frame (every output then
-// holds nframes + 1; nframes may be 0) and copied there.
+// holds nframes + 1; nframes may be 0) and copied there, and kClearWords words at
+// `clear` (or null) are set to 0.
 constexpr int kFirstMax = 512;
+constexpr int kClearWords = 20;
 hipError_t launch_row_pass(int n, int in_dtype, const void* frames, const void* ref,
                            const float* window, int nframes, float2* inter, double* rowsum,
                            double* rowabs, float* nyq, const float2* tw, void* ref_out,
-                           hipStream_t s);
+                           uint32_t* clear, hipStream_t s);
 
 // Fused row and column passes of `nframes` frames (n = 1024 only) in one
 // persistent launch of `workers` workgroups: per-XCD task queues, the
