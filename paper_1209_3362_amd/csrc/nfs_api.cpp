@@ -337,15 +337,17 @@ int64_t next_batch(const nfs_plan_s* h, int64_t left, BatchScratch* scratch) {
   return best;
 }
 
-// Sum the pending pairs if pushing `b` more frames would overwrite a
-// spectrum one of them needs: frames [t_pushed, t_pushed + b) evict frames
-// up to t_pushed + b - 1 - capacity, and pending pairs need the frames from
+// End of the frames that overwrite no spectrum a pending pair needs: frame t
+// evicts frame t - capacity, and pending pairs need the frames from
 // max(0, t_done - max_lag) on.
+int64_t room_end(const nfs_plan_s* h) {
+  return h->L.capacity + std::max<int64_t>(h->t_done - h->L.max_lag, 0);
+}
+
+// Sum the pending pairs if pushing `b` more frames would overwrite a
+// spectrum one of them needs.
 nfs_status make_room(nfs_plan_s* h, int64_t b) {
-  const nfs::Layout& L = h->L;
-  const int64_t needed = h->t_done - L.max_lag > 0 ? h->t_done - L.max_lag : 0;
-  if (h->t_pushed + b - L.capacity > needed) return flush_pairs(h);
-  return NFS_OK;
+  return h->t_pushed + b > room_end(h) ? flush_pairs(h) : NFS_OK;
 }
 
 // Normalise, transform and store `b` frames (device memory, b <= the batch
@@ -631,14 +633,24 @@ nfs_status nfs_push_frames(nfs_handle h, const void* frames, int64_t count) {
   if (count < 0) return fail(h, NFS_E_ARG, "count must be >= 0");
   if (count == 0) return NFS_OK;
   if (!frames) return fail(h, NFS_E_ARG, "frames is NULL");
+  // Pending pairs are summed before the same frames as when the plan's own
+  // batches are pushed (host frames), so that the sums do not depend on where
+  // frames come from: `step` frames are a plan's batch.
+  const int64_t step = next_batch(h, h->L.capacity), t0 = h->t_pushed;
   int64_t i = 0;
   while (i < count) {
+    if (i % step == 0) {
+      nfs_status st = make_room(h, std::min(step, count - i));
+      if (st != NFS_OK) return st;
+    }
+    // Frames up to the next plan's batch that there is no room for.
+    const int64_t limit = room_end(h) - t0;
+    int64_t end = count <= limit ? count : limit / step * step;
+    end = std::max(end, std::min(count, (i / step + 1) * step));
     BatchScratch w;
-    const int64_t b = next_batch(h, count - i, &w);
-    nfs_status st = make_room(h, b);
-    if (st == NFS_OK)
-      st = transform_batch(h, static_cast<const char*>(frames) + size_t(i) * h->L.frame_bytes, b,
-                           w);
+    const int64_t b = next_batch(h, end - i, &w);
+    nfs_status st = transform_batch(
+        h, static_cast<const char*>(frames) + size_t(i) * h->L.frame_bytes, b, w);
     if (st != NFS_OK) return st;
     i += b;
   }
