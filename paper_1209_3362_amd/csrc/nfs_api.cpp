@@ -153,7 +153,7 @@ hipError_t flush_pairs_mx(nfs_plan_s* h, const std::vector<nfs::MxGroup>& groups
     while (t < T1) {
       const int64_t e = tb < 0 ? T1 : nfs::mx_cut(t, T1, ta, tb);
       nfs::MxShape s = nfs::mx_shape(t, e, ta, tb < 0 ? ta : tb);
-      nfs::mx_workgroup(&s, L.slots);
+      nfs::mx_workgroup(&s, L.ring_slots);
       nfs::mx_tables(L.lags, g, t, e, &tab);
       hipError_t err = nfs::launch_pairs_mx(
           h->ring, L.spec_dtype, h->refspec, h->fscale, L.slots, L.mode_stride, L.capacity, s,
@@ -182,7 +182,10 @@ nfs_status flush_pairs(nfs_plan_s* h) {
   for (const nfs::LagGroup& g : h->groups) {
     hipError_t e = hipSuccess;
     nfs::WindowShape w;
-    if (L.accum == NFS_ACC_PLAIN && nfs::window_shape(g, L.slots, h->t_done, h->t_pushed, &w)) {
+    // The shapes of a full-spectra plan are those of the ring plan, so that the
+    // sums of the modes that both store are the same bit for bit.
+    if (L.accum == NFS_ACC_PLAIN &&
+        nfs::window_shape(g, L.ring_slots, h->t_done, h->t_pushed, &w)) {
       e = nfs::launch_pairs_window(h->ring, L.spec_dtype, h->refspec, h->fscale, L.slots,
                                    L.mode_stride, L.capacity, h->t_done, h->t_pushed,
                                    h->lags + g.first, w, h->acc + g.first, L.n_lags,

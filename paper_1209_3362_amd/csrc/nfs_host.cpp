@@ -119,7 +119,9 @@ nfs_status make_layout(const nfs_desc* d, size_t bytes_available, Layout* L,
   o.tiles.assign(size_t(2 * T + 1), 0);
   int64_t base = 0;
   for (int t = 0; t < T; ++t) {
-    const int R = o.full ? o.h : int(isqrt_u64(uint64_t(hh - 1 - int64_t(8 * t) * (8 * t))));
+    const int ring_R = int(isqrt_u64(uint64_t(hh - 1 - int64_t(8 * t) * (8 * t))));
+    const int R = o.full ? o.h : ring_R;
+    o.ring_slots += 8 * (2 * int64_t(ring_R) + 1);
     o.tiles[size_t(t)] = int32_t(base);
     o.tiles[size_t(T + 1 + t)] = R;
     base += o.full ? 8 * int64_t(o.n) : 8 * (2 * int64_t(R) + 1);

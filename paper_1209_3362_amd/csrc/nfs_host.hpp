@@ -48,6 +48,7 @@ struct Layout {
   int mode_bytes = 8;      // bytes per stored mode in the ring
   int64_t modes = 0;       // M: stored modes per spectrum (those in a ring)
   int64_t slots = 0;       // slots per spectrum in the tiled layout (>= M)
+  int64_t ring_slots = 0;  // slots of a plan of this n that stores the ring modes only
   int64_t mode_stride = 0; // slots rounded up to 64: ring slot and sum-row pitch
   int64_t capacity = 0;    // ring slots
   int batch = 0;           // frames per transform launch

@@ -70,7 +70,7 @@ struct WindowShape {
   size_t lds = 0;
 };
 
-// The shape for one lag group of a plan with n_modes slots; false where the
+// The shape for one lag group of a plan with n_modes slots (about); false where the
 // window is left to the group's other kernels.
 bool window_shape(const LagGroup& group, int64_t n_modes, int64_t T0, int64_t T1,
                   WindowShape* w);
