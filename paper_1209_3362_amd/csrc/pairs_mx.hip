@@ -372,20 +372,29 @@ __device__ __forceinline__ void sum_small(const MxArgs& a, int64_t m0) {
       if (!mask) continue;
       const bool mine = mask >> lane & 1;
       const int64_t lag0 = a.lags[l0 + __builtin_ctzll(mask)];
+      const int64_t lag1 = a.lags[l0 + 63 - __builtin_clzll(mask)];
       const int64_t tau = mine ? int64_t(a.lags[l0 + lane]) : lag0;
-      // Targets t0 + r, r >= first, and the older frames' places.
-      const int first = mine ? int(max(tau - a.t0, int64_t(0))) : tn;
+      // Targets t0 + r, r >= first, and the older frames' places. From r1 on every
+      // delay has pairs.
+      const int first = int(max(tau - a.t0, int64_t(0)));
+      const int r1 = int(max(lag1 - a.t0, int64_t(0)));
+      const float2* target = z + a.tbase;
       const int older = int(a.t0 - tau - a.olo) + a.obase;
       double sum = 0.0;
-      for (int r = int(max(lag0 - a.t0, int64_t(0))); r < tn; r += 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float2 x = z[a.tbase + min(r + i, tn - 1)];
-          const float2 o = z[min(max(older + r + i, 0), pl - 1)];
-          const float dx = x.x - o.x, dy = x.y - o.y;
-          if (r + i >= first && r + i < tn) sum += double(fmaf(dx, dx, dy * dy));
-        }
+      auto square = [&](int r, float2 o) {
+        const float dx = target[r].x - o.x, dy = target[r].y - o.y;
+        return double(fmaf(dx, dx, dy * dy));
+      };
+      int r = int(max(lag0 - a.t0, int64_t(0)));
+      for (; r < r1; ++r) {
+        const double d = square(r, z[max(older + r, 0)]);
+        if (r >= first) sum += d;
       }
+      for (; r + 8 <= tn; r += 8) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += square(r + i, z[older + r + i]);
+      }
+      for (; r < tn; ++r) sum += square(r, z[older + r]);
       if (mine) add_sum(a, m0 + mm, l0 + lane, float(sum));
     }
   }
