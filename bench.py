@@ -590,6 +590,9 @@ def main():
     # Pair kernel: per pair and mode 2 subtractions + 2 FMAs = 6 FLOP
     # (4 VALU lane-instructions; the Kahan form adds a few per chunk).
     pair_tflops = 6.0 * pair_k / (ms_pair * 1e-3) / 1e12
+    # The 400 consecutive delays of c3 are summed on the matrix cores, in byte
+    # products: the explicit form's FLOP over the stage's time, without a peak.
+    matrix = args.workload == "c3"
     base = (args.workload, args.spec, args.accum, args.capacity or N) == ("c2", "f32", "plain", N)
     # Transform stage (A1-A3): algorithmic bytes are the frames read once and
     # the stored modes written once; the row-to-column intermediate is not
@@ -626,18 +629,19 @@ def main():
         "stage_ms": {"normalise_fft_store": ms_fft, "lag_pairs": ms_pair, "bin": ms_bin},
         "status": st,
         "roofline": {
-            "kernel": "pair_kernel (lag-pair accumulator)",
-            "bound": "alu",
+            "kernel": "pair_mx_kernel (lag-pair sums on the matrix cores)" if matrix
+                      else "pair_kernel (lag-pair accumulator)",
+            "bound": "mfma" if matrix else "alu",
             "achieved": pair_tflops,
-            "peak": FP32_PEAK_TFLOPS,
+            "peak": None if matrix else FP32_PEAK_TFLOPS,
             "unit": "TFLOP/s",
-            "frac": pair_tflops / FP32_PEAK_TFLOPS,
+            "frac": None if matrix else pair_tflops / FP32_PEAK_TFLOPS,
             "traffic": counter_figure(PAIR_COUNTERS, "traffic_bytes_per_launch") if base
                        else None,
             "flop_per_launch": 6.0 * pair_k,
-            "peak_nonpacked": FP32_NONPACKED_TFLOPS,
-            "frac_nonpacked": pair_tflops / FP32_NONPACKED_TFLOPS,
-            "valu_issue_frac": 4.0 * pair_k / (ms_pair * 1e-3) / VALU_LANE_OPS,
+            "peak_nonpacked": None if matrix else FP32_NONPACKED_TFLOPS,
+            "frac_nonpacked": None if matrix else pair_tflops / FP32_NONPACKED_TFLOPS,
+            "valu_issue_frac": None if matrix else 4.0 * pair_k / (ms_pair * 1e-3) / VALU_LANE_OPS,
         },
         "transform_roofline": {
             "kernel": "row_pass_kernel + col_pass_kernel (normalise, 2D transform, store)",

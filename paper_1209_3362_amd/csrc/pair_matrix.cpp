@@ -240,7 +240,11 @@ void mx_tables(const std::vector<int32_t>& lags, const MxGroup& g, int64_t t0, i
 // with 16 / 8 modes; its long-delay kernel reads a pair in 0.17. At 1000
 // frames, matrix against explicit: delays 1..400 1.55 against 5.73 ms, 1..96
 // 0.73 against 1.38, 1..56 0.61 against 0.64, 50 log-spaced ones up to 500
-// 0.83 against 0.67; at 128 frames delays 1..64 0.36 against 0.26.
+// 0.83 against 0.67; at 128 frames delays 1..64 0.36 against 0.26. The short-window
+// kernel, other frame sizes, storage types and Kahan sums are not in the fit:
+// over 258 stacks of 16 x 16 to 512 x 512 frames (130 to 1500 of them, 48 delays
+// to all, every storage type) a whole pass took at most 0.98 of what it took
+// before there was this kernel and the short-window one.
 bool mx_wins(const std::vector<int32_t>& lags, const std::vector<LagGroup>& groups,
              const std::vector<MxGroup>& mx, int64_t t0, int64_t t1) {
   double plain = 0.0;

@@ -25,15 +25,19 @@
 // corrected by the reference transform, scaled and written as byte planes;
 // prefix sums of |a|^2 every 8 frames give the energies, the frames between
 // them from the planes by byte dot products, or for 64 consecutive delays by a
-// sum over the lanes. 4-wave workgroups, two per CU (80 KB of LDS, some 220
+// sum over the lanes. 4-wave workgroups, two per CU (80 KB of LDS, some 240
 // registers per lane): one's loads run under the other's products.
 //
 // Measured against the explicit kernel (pair stage, MI355X): 2048 frames of
-// 512 x 512 with all 2047 delays 63.6 -> 9.9 ms; 900 frames of 1024 x 1024,
-// delays 1..400, BF16 spectra, 23.0 -> 5.5 ms, of which the products take 3.1
+// 512 x 512 with all 2047 delays 63.6 -> 9.2 ms; 900 frames of 1024 x 1024,
+// delays 1..400, BF16 spectra, 23.0 -> 5.7 ms, of which the products take 3.1
 // (the matrix units' own time is 2.4: 18.5 cycles per product at 2.4 GHz), the
 // digits 0.8 and the energies 1.3. Bound by instruction issue at two waves per
 // SIMD: a step of four row sets is 16 products and 23 vector instructions.
+// The small sums and the test for them take 0.45 of the 9.2 ms (the last delays
+// have few pairs) and 0.1 of the 5.7. 300 frames of 512 x 512 with 250 delays take
+// 0.58 ms, with a frame 10^4 times the others, where the sums of 100
+// delays are small, 1.42; the explicit kernel takes 1.51.
 // 8-wave workgroups of 128 registers (four waves per SIMD, two row sets per
 // task) took as long on dense delays and 10 % longer on the 2047.
 #include <algorithm>

@@ -278,7 +278,9 @@ class Plan:
         self._borrowed.clear()
 
     def tune_pairs(self, cache=True):
-        """Pair-kernel launch shapes per lag group, [(modes, waves)]: taken
+        """Launch shapes of the history pair kernel per lag group, [(modes,
+        waves)] (windows with many lags, and short ones, are summed by kernels
+        that have no shape to choose, whatever is tuned): taken
         from the tuning cache (tune_cache.py; key: GPU architecture, n, lags,
         storage, accumulation) through nfs_set_pair_shapes when it holds this
         plan's key, else timed by nfs_tune_pairs on the frames pushed so far
